@@ -8,7 +8,8 @@ MLUPS counts every lattice point, solid or fluid (the paper's convention).
 
 Printed JSON line (rank 0, stdout): the contract fields, plus
   roofline      achieved HBM GB/s of the step kernel from the algorithmic
-                152 B per point (19 loads + 19 stores of 4 B, Section 4.1)
+                152 B per point and launch (19 loads + 19 stores of 4 B,
+                Section 4.1; the two-step kernel takes two steps for them)
                 over its average duration, vs the 8 TB/s MI355X peak;
   cpu_baseline  the FP64 oracle timed on the host cores on a bounded sample;
   extra         16-bit offset storage (two-array and in-place AA) rates, the
@@ -62,7 +63,7 @@ def kernel_source_hash():
     with the counter summaries so that the benchmark reports traffic only for
     the kernels the counters were taken on."""
     h = hashlib.sha256()
-    for name in ("d3q19.hpp", "kernels_step.hip", "kernels.hpp"):
+    for name in ("d3q19.hpp", "kernels_step.hip", "kernels_pair.hip", "kernels.hpp"):
         with open(os.path.join(ROOT, "paper_1309_1983_amd", "csrc", name), encoding="utf-8") as fh:
             h.update(_code_of(fh.read()).encode())
     return h.hexdigest()[:16]
@@ -136,11 +137,12 @@ def _pmc_table(path):
 
 def _algorithmic_bytes_per_point(kernel):
     """State bytes one launch must move per lattice point (Section 4.1): 19
-    loads and 19 stores of the storage width for a step, plus the force field
-    when the step reads one; 264 B for the reverse step; None otherwise."""
+    loads and 19 stores of the storage width for a step or for the two steps
+    of the two-step kernel, plus the force field when the step reads one;
+    264 B for the reverse step; None otherwise."""
     if kernel.startswith("lbmk::k_adj_stepv"):
         return ADJOINT_REVERSE_BYTES
-    for pre in ("lbmk::k_step_abv<", "lbmk::k_step_aa0<", "lbmk::k_step_aa1<"):
+    for pre in ("lbmk::k_step_pair<", "lbmk::k_step_abv<", "lbmk::k_step_aa0<", "lbmk::k_step_aa1<"):
         if kernel.startswith(pre):
             args = [a.strip() for a in kernel[len(pre):-1].split(",")]
             width = 4 if args[0].endswith("StF32") else 2
@@ -228,6 +230,12 @@ def time_steps(lat, steps, torch, stream_only=False):
     e1.record(s)
     torch.cuda.synchronize()
     return e0.elapsed_time(e1) / steps
+
+
+def step_bytes(lat, storage):
+    """Algorithmic bytes per point and step: the state read and written once
+    per launch, and the steps that the launch takes."""
+    return BYTES_PER_POINT[storage] / (2 if "k_step_pair" in lat.step_kernel_name() else 1)
 
 
 def cavity_lattice(n, storage, pattern, tau, lid, block=None, cells_per_lane=0, onsite=False):
@@ -368,19 +376,19 @@ def config_rates(torch, steps):
         lat.set_force((0.0, 0.0, 1e-6))
         lat.step(20)
         m = time_steps(lat, steps, torch)
+        bpp = step_bytes(lat, storage)
         lat.close()
-        bpp = BYTES_PER_POINT[storage]
         out[f"spheres128x128x256_{storage}_{pattern}"] = {
             "mlups": round(N / m / 1e3, 1), "fluid_mlups": round(nfl / m / 1e3, 1),
             "ms_per_step": round(m, 5), "gbs": round(bpp * N / m / 1e6, 1),
-            "frac": round(bpp * N / m / 1e6 / HBM_PEAK_GBS, 4), "fluid_fraction": round(nfl / N, 4)}
+            "frac": round(bpp * N / m / 1e6 / HBM_PEAK_GBS, 4), "bytes_per_point": bpp, "fluid_fraction": round(nfl / N, 4)}
     for storage, pattern in (("f32", "ab"), ("f16", "aa")):
         lat = cavity_lattice(512, storage, pattern, 0.55, 0.05)
         lat.step(4)
         m = time_steps(lat, max(100, steps // 5), torch)
+        bpp = step_bytes(lat, storage)
         lat.close()
         torch.cuda.empty_cache()
-        bpp = BYTES_PER_POINT[storage]
         N = 512 ** 3
         out[f"cavity512_{storage}_{pattern}"] = {
             "mlups": round(N / m / 1e3, 1), "ms_per_step": round(m, 5), "gbs": round(bpp * N / m / 1e6, 1),
@@ -646,9 +654,10 @@ def main():
     log(f"timing {args.steps} FP32 AB steps ({kernel_name})")
     ms = time_steps(lat, args.steps, torch)
     lat.check_finite()
+    bpp = step_bytes(lat, "f32")
     lat.close()
     mlups = N / ms / 1e3
-    achieved = BYTES_PER_POINT["f32"] * N / (ms * 1e-3) / 1e9
+    achieved = bpp * N / (ms * 1e-3) / 1e9
     traffic = load_traffic(workload, kernel_name)
     line = {
         "metric": "MLUPS and % HBM roofline, D3Q19 FP32 256^3; FP16-storage and adjoint MLUPS",
@@ -662,7 +671,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
-                     "bytes_per_point": BYTES_PER_POINT["f32"],
+                     "bytes_per_point": bpp, "steps_per_launch": round(BYTES_PER_POINT["f32"] / bpp),
                      "kernel": kernel_name},
     }
     # the paper's own figure, on other hardware: context only, not vs_baseline
@@ -698,8 +707,8 @@ def main():
             lat = cavity_lattice(n, storage, pattern, tau, lid, cells_per_lane=cpl)
             lat.step(args.warmup)
             m = time_steps(lat, args.steps, torch)
+            bpp = step_bytes(lat, storage)
             lat.close()
-            bpp = BYTES_PER_POINT[storage]
             gbs = bpp * N / (m * 1e-3) / 1e9
             key = f"{storage}_{pattern}" + (f"_w{cpl}" if cpl else "")
             extra[key] = {"mlups": round(N / m / 1e3, 1), "ms_per_step": round(m, 5),
@@ -711,11 +720,12 @@ def main():
         lat.step(args.warmup)
         m = time_steps(lat, args.steps, torch)
         lat.check_finite()
+        bpp = step_bytes(lat, "f32")
         lat.close()
-        gbs = BYTES_PER_POINT["f32"] * N / (m * 1e-3) / 1e9
+        gbs = bpp * N / (m * 1e-3) / 1e9
         extra["f32_ab_onsite_walls"] = {"mlups": round(N / m / 1e3, 1), "ms_per_step": round(m, 5),
                                         "gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
-                                        "bytes_per_point": BYTES_PER_POINT["f32"]}
+                                        "bytes_per_point": bpp}
         log(f"f32_ab on-site walls: {m:.4f} ms/step, {N / m / 1e3:.0f} MLUPS, {gbs:.0f} GB/s")
         # the step with rho and u stored every step (four extra stores per point)
         lat = cavity_lattice(n, "f32", "ab", tau, lid)

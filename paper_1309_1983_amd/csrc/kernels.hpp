@@ -53,6 +53,24 @@ hipError_t launch_step_abv(int storage, int vw, bool collide, int force_mode, vo
                            const float* ffield, const StepArgs& args, const Launch& L,
                            float* rho = nullptr, float* u = nullptr, bool onsite = false);
 
+// Two AB steps in one launch (kernels_pair.hip). A work-group of `threads`
+// work-items computes tx x (rows - 2) columns over `depth` planes; a tile row
+// takes PAIR_PITCH points of LDS, halo columns included.
+constexpr int PAIR_MAX_THREADS = 1024;
+constexpr int PAIR_PITCH = 68;
+struct PairShape {
+    uint32_t tx, rows, depth;
+    uint32_t ntx, nty, groups;   // tiles in x and y, work-groups in all
+    uint32_t threads;
+};
+// `a` holds the state, `b` receives the state two steps later. walls: the
+// lattice has solid points (FP32 storage only); moving: some of them move.
+// name non-null: reports the kernel instead of launching it.
+hipError_t launch_step_pair(int storage, int force_mode, const void* a, void* b, const uint8_t* flags,
+                            const uint32_t* smask, const uint32_t* mmask, const float* ffield, const StepArgs& args,
+                            const PairShape& ps, bool walls, bool moving, hipStream_t s,
+                            const void** name = nullptr);
+
 // The kernel (host-side function pointer) that launch_step_abv (vector) or
 // launch_step would launch with these arguments, without launching it.
 hipError_t resolve_step_kernel(bool vector, int storage, int pattern, int parity, int vw, bool collide,

@@ -80,6 +80,9 @@ struct lbm_lattice {
     bool alt_flat = false;
     bool onsite = false;           // has on-site velocity nodes (flags 3, 4)
     bool early = false;            // FP32 vector AB step gathers before the flag branches
+    bool pair = false;             // AB steps are taken two per launch where possible
+    lbmk::PairShape pair_shape{};
+    bool walls = false, moving = false;   // has solid points / moving ones
     unsigned shmem4 = 0;           // LDS reserved per vector-step work-group (residency cap)
     hipEvent_t order_ev = nullptr; // orders work across lbm_set_stream
 
@@ -193,6 +196,10 @@ lbmk::StepArgs step_args(const lbm_lattice* L)
     a.early = L->early ? 1u : 0u;
     return a;
 }
+
+// Steps may be taken two per launch: the per-step event log needs them one
+// by one, and so does a finite check after every step.
+bool takes_pairs(const lbm_lattice* L) { return L->pair && L->events.empty() && L->check_interval != 1; }
 
 lbmk::Launch launch_of(const lbm_lattice* L) { return lbmk::make_launch(L->dims, L->bx, L->by, L->stream); }
 
@@ -452,6 +459,65 @@ constexpr size_t SMALL_PERIODIC_MAX_POINTS = (size_t)1 << 18;
 // kernel's registers allow, 412 us at 8, 415 us at 10, 438 us at 5.
 constexpr int AUTO_GROUPS_PER_CU_F32 = 8;
 
+// Tiling of the two-step kernel for an nx x ny x nz lattice, and whether two
+// steps in one launch take less time than two launches of one step.
+//
+// One work-group is resident per compute unit (its LDS and registers fill
+// it), so a launch takes `rounds` = work-groups / compute units, rounded up,
+// times the planes that one of them computes (two more than it stores). The
+// times are MI355X measurements: a plane of 1024 work-items takes 6.0 us
+// (periodic 256^3), 6.4 us (walled duct, cavity) to 8 us (10%-solid sphere
+// duct) in FP32 and 4.3 us with 16-bit storage, and the first plane's loads 4
+// us. Two steps, pair against single kernels, us: cavity 256^3 555 / 813,
+// cavity 128^3 95 / 120, cavity 96^3 49 / 66, sphere duct 128x128x256 183 /
+// 228, periodic 256^3 FP16 381 / 522; but cavity 64^3 26 / 19: too few planes
+// per work-group to pay for the two extra ones.
+//
+// 16-bit storage takes pairs only without solid points: there the kernel is
+// bound by its memory instructions and arithmetic rather than by HBM, and
+// with walls it only drew level (256^3 FP16 cavity 436 / 446 us) or lost
+// (sphere duct 150 / 134).
+bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::PairShape& best)
+{
+    const bool f32 = storage == LBM_STORAGE_F32;
+    if (!f32 && walls) return false;
+    if ((unsigned long long)nx * ny > (1ull << 28) || nx < 2) return false;
+    const double N = (double)nx * ny * nz;
+    // a single step: bytes at the rate its kernel reaches, plus its launch
+    const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
+    const double rate = f32 ? (nx % 4 == 0 ? 5.6e6 : 4.6e6) : (nx % 4 == 0 ? 4.7e6 : 3.7e6);   // bytes per us
+    const double single = bytes / rate + 2.5;
+    lbmk::PairShape ps{};
+    const int widest = lbmk::PAIR_PITCH - 2, tallest = lbmk::PAIR_MAX_THREADS / lbmk::PAIR_PITCH - 2;
+    ps.ntx = (uint32_t)((nx + widest - 1) / widest);
+    ps.tx = (uint32_t)((nx + (int)ps.ntx - 1) / (int)ps.ntx);
+    // rows that start on 64-byte lines: so do the tiles (160-point rows: 64
+    // columns 183 us, 54 columns 232 us per two steps)
+    if (nx % 16 == 0) ps.tx = std::min((ps.tx + 15u) / 16u * 16u, (uint32_t)widest / 16u * 16u);
+    ps.ntx = (uint32_t)((nx + (int)ps.tx - 1) / (int)ps.tx);
+    ps.nty = (uint32_t)((ny + tallest - 1) / tallest);
+    ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
+    ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
+    ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
+    const double plane = (f32 ? (walls ? 6.6 : 6.1) : 4.4) * std::max(0.5, ps.threads / 1024.0);
+    double least = 0.0;
+    for (int c = 1; c <= nz; ++c) {
+        const int depth = (nz + c - 1) / c;
+        const unsigned long long chunks = (unsigned long long)((nz + depth - 1) / depth);
+        const unsigned long long groups = chunks * ps.ntx * ps.nty;
+        if (groups > (1ull << 30)) break;
+        const double rounds = std::ceil((double)groups / cus);
+        const double us = rounds * ((depth + 2) * plane + 4.0);
+        if (best.groups == 0 || us < least) {
+            least = us;
+            ps.depth = (uint32_t)depth;
+            ps.groups = (uint32_t)groups;
+            best = ps;
+        }
+    }
+    return best.groups > 0 && least < 0.95 * 2.0 * single;
+}
+
 }  // namespace
 
 extern "C" {
@@ -513,12 +579,18 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
         if (nbuf == 2 && opt.population_dev[0] == opt.population_dev[1])
             return fail(LBM_ERR_INVALID, "population_dev[0] and [1] must be different buffers");
     }
-    bool onsite = false;
+    bool onsite = false, moving = false;
     if (flags_host) {
+        // one pass that vectorises; the offending point is looked for only if there is one
+        uint8_t largest = 0, two = 0;
         for (unsigned long long c = 0; c < N; ++c) {
-            if (flags_host[c] > 4) return fail(LBM_ERR_INVALID, "flag value %u at point %llu (allowed 0..4)", flags_host[c], c);
-            onsite = onsite || flags_host[c] >= 3;
+            largest = std::max(largest, flags_host[c]);
+            two |= (uint8_t)(flags_host[c] == 2);
         }
+        for (unsigned long long c = 0; largest > 4 && c < N; ++c)
+            if (flags_host[c] > 4) return fail(LBM_ERR_INVALID, "flag value %u at point %llu (allowed 0..4)", flags_host[c], c);
+        onsite = largest >= 3;
+        moving = two != 0;
     }
 
     int dev = opt.device;
@@ -543,6 +615,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     L->cpl = lay.cpl;
     L->vec_ok = opt.cells_per_lane != 1;
     L->onsite = onsite;
+    L->moving = moving;
     if (lay.cpl > 1) { L->bx4 = lay.bx4; L->by4 = lay.by4; L->flat = lay.flat; }
 
     lbm_status st = LBM_OK;
@@ -621,6 +694,18 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             L->alt4 = true; L->alt_bx4 = l4.bx4; L->alt_by4 = l4.by4; L->alt_flat = l4.flat;
         }
         g_last_error.clear();
+    }
+    L->walls = (size_t)(unsigned)counts[2] != L->N;
+    if (L->pattern == LBM_PATTERN_AB && !L->onsite && opt.cells_per_lane == 0 && opt.gather_mode == 0 &&
+        opt.groups_per_cu == 0 && opt.block_x == 0 && opt.block_y == 0) {
+        // two steps per launch, unless an option asks for a form of the one-step kernel
+        int cus = 0;
+        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess || cus <= 0) {
+            lbm_destroy(L);
+            return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
+        }
+        L->pair = plan_pair(nx, ny, nz, L->storage, L->walls, cus, L->pair_shape);
     }
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
     L->early = early_ok && (opt.gather_mode == 2 ||
@@ -749,7 +834,11 @@ lbm_status lbm_step_kernel_name(lbm_lattice* L, char* buf, size_t cap)
     DeviceGuard guard(L->device);
     const bool vector = L->pattern == LBM_PATTERN_AB && L->cpl > 1;
     const void* fn = nullptr;
-    HIPCHK(L, lbmk::resolve_step_kernel(vector, L->storage, L->pattern, L->parity, vec_shape(L).cpl, true, force_mode(L),
+    if (takes_pairs(L))
+        HIPCHK(L, lbmk::launch_step_pair(L->storage, force_mode(L), nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                         step_args(L), L->pair_shape, L->walls, L->moving, L->stream, &fn));
+    else
+        HIPCHK(L, lbmk::resolve_step_kernel(vector, L->storage, L->pattern, L->parity, vec_shape(L).cpl, true, force_mode(L),
                                         L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags, L->d_smask, L->d_mmask,
                                         L->d_force, step_args(L), vector ? launch4_of(L) : launch_of(L), L->onsite,
                                         &fn));
@@ -1202,7 +1291,24 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u)
         HIPCHK(L, hipEventRecord(L->events[0], L->stream));
         L->ev_recorded = 1;
     }
+    const bool pairs = collide && takes_pairs(L);
     for (int s = 0; s < n; ++s) {
+        // two steps in one launch, unless the second is the one that stores
+        // rho and u or a finite check is due in between
+        if (pairs && n - s >= 2 && !(rho && n - s == 2) &&
+            (L->check_interval == 0 || (L->steps_done + 1) % L->check_interval != 0)) {
+            HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags, L->d_smask,
+                                             L->d_mmask, L->d_force, args, L->pair_shape, L->walls, L->moving,
+                                             L->stream));
+            L->cur ^= 1;
+            L->steps_done += 2;
+            ++s;
+            if (L->check_interval > 0 && L->steps_done % L->check_interval == 0) {
+                lbm_status st = lbm_check_finite(L);
+                if (st != LBM_OK) return st;
+            }
+            continue;
+        }
         float* mr = s == n - 1 ? rho : nullptr;
         float* mu = s == n - 1 ? u : nullptr;
         if (L->pattern == LBM_PATTERN_AB && L->cpl > 1) {
