@@ -176,7 +176,25 @@ struct Dims {
     int nx, ny, nz;
     uint32_t nxy;   // nx*ny
     uint32_t N;     // nx*ny*nz (< 2^30)
+    uint32_t flat;  // one-point kernels: 1 = one-dimensional grid over the points of a plane
 };
+
+// The point of this work-item in a launch of one point per work-item; false
+// outside the plane. Rows that are not a multiple of a wave run on a
+// one-dimensional grid over the plane, so that every wave is full.
+__device__ __forceinline__ bool point_of(const Dims& d, int& x, int& y)
+{
+    if (d.flat) {
+        const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+        const uint32_t row = k / (uint32_t)d.nx;
+        y = (int)row;
+        x = (int)(k - row * (uint32_t)d.nx);
+        return k < d.nxy;
+    }
+    x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    y = (int)(blockIdx.y * blockDim.y + threadIdx.y);
+    return x < d.nx && y < d.ny;
+}
 
 // Population storage: the values of direction i in z-slab z form one plane of
 // nx*ny elements, f[(z*Q + i)*nxy + y*nx + x]. All work-items of a work-group

@@ -20,6 +20,7 @@ struct StepArgs {
     uint32_t gx;                // vector AB step: > 0 = its grid is one-dimensional in x over
                                 // the gx * ny point groups of a z-plane (gx = nx / vw groups
                                 // per row, x fastest); 0 = two-dimensional (x groups, y)
+    uint32_t agx;               // the same for the vector reverse step: groups per row, 0 = two-dimensional
     uint32_t early;             // FP32 vector AB step: issue the gather before the flag
                                 // branches (porous geometry)
 };

@@ -45,10 +45,9 @@ __global__ __launch_bounds__(1024) void k_adj_seed(const float* __restrict__ f,
                                                    StepArgs a)
 {
     const Dims& d = a.d;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int x, y;
+    if (!point_of(d, x, y)) return;
     const uint32_t z = blockIdx.z;
-    if (x >= d.nx || y >= d.ny) return;
     const uint32_t o = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
     const uint32_t c = z * d.nxy + o;
     const size_t N = d.N;
@@ -173,10 +172,9 @@ __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
 {
     constexpr bool FORCE = FM != FORCE_NONE;
     const Dims& d = a.d;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int x, y;
+    const bool inside = point_of(d, x, y);
     const uint32_t z = blockIdx.z;
-    const bool inside = x < d.nx && y < d.ny;
     const uint32_t o = inside ? (uint32_t)y * (uint32_t)d.nx + (uint32_t)x : 0u;
     const uint32_t c = z * d.nxy + o;
     const uint8_t fl = inside ? flags[c] : (uint8_t)1;
@@ -270,8 +268,16 @@ __global__ __launch_bounds__(256, 3) void k_adj_stepv(const float* __restrict__ 
     constexpr bool FORCE = FM != FORCE_NONE;
     constexpr FW ONES = FlagBytes<VW>::ones;
     const Dims& d = a.d;
-    const int x0 = VW * (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    // agx > 0: rows whose group count does not divide into waves run on a
+    // one-dimensional grid over the plane (agx groups per row)
+    int x0 = VW * (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    int y = blockIdx.y * blockDim.y + threadIdx.y;
+    if (a.agx) {
+        const uint32_t g = blockIdx.x * blockDim.x + threadIdx.x;
+        const uint32_t row = g / a.agx;
+        x0 = VW * (int)(g - row * a.agx);
+        y = (int)row;
+    }
     const uint32_t z = blockIdx.z;
     const bool inside = x0 < d.nx && y < d.ny;
     const uint32_t nx = (uint32_t)d.nx;
@@ -434,7 +440,6 @@ hipError_t launch_adjoint_stepv(int vw, bool direct, int fm, const float* s, con
                                 float inv_tau2, const Launch& L)
 {
     if (vw == 2) return adjv_vw<2>(direct, fm, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
-    if (vw == 4) return adjv_vw<4>(direct, fm, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
     return hipErrorInvalidValue;
 }
 

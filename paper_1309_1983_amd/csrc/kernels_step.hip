@@ -20,6 +20,12 @@ Launch make_launch(const Dims& d, int bx, int by, hipStream_t s)
 {
     Launch L;
     L.block = dim3((unsigned)bx, (unsigned)by, 1);
+    if (d.flat) {
+        L.block = dim3((unsigned)(bx * by), 1, 1);
+        L.grid = dim3((d.nxy + L.block.x - 1) / L.block.x, 1, (unsigned)d.nz);
+        L.stream = s;
+        return L;
+    }
     L.grid = dim3((unsigned)((d.nx + bx - 1) / bx), (unsigned)((d.ny + by - 1) / by), (unsigned)d.nz);
     L.stream = s;
     return L;
@@ -66,10 +72,9 @@ __device__ __forceinline__ Macro decode_collide(const typename St::raw_t raw[Q],
 }
 
 #define POINT_PROLOGUE(d)                                                                      \
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;                                       \
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;                                       \
+    int x, y;                                                                                  \
+    if (!point_of((d), x, y)) return;                                                          \
     const uint32_t z = blockIdx.z;                                                             \
-    if (x >= (d).nx || y >= (d).ny) return;                                                    \
     const uint32_t o = (uint32_t)y * (uint32_t)(d).nx + (uint32_t)x;                           \
     const uint32_t c = z * (d).nxy + o;                                                        \
     const uint32_t zm = wrap_m(z, (uint32_t)(d).nz), zp = wrap_p(z, (uint32_t)(d).nz);

@@ -217,11 +217,22 @@ lbmk::Launch launch4_of(const lbm_lattice* L)
         return la;
     }
     d3q19::Dims q = L->dims;
+    q.flat = 0;
     q.nx = L->nx / v.cpl;   // the grid counts groups of cpl points along x
     lbmk::Launch la = lbmk::make_launch(q, v.bx4, v.by4, L->stream);
     la.shmem = L->shmem4;
     return la;
 }
+
+// Rows of n work-items fill their waves on a two-dimensional grid: n is a
+// multiple of 64, or several rows make up a wave. Other rows leave lanes idle
+// there (131 points take three waves, the last with 3 of 64 lanes; 33
+// four-point groups half a wave) and run on a one-dimensional grid over the
+// plane instead. MI355X, us per step, two- against one-dimensional: on-site
+// cavity 132x131x131 (33 groups a row) 99.3 / 82.8; 131x97x75 sphere duct, one
+// point per work-item, FP32 31.1 / 29.6, FP16 20.2 / 18.8; 192^3 duct with a
+// force and rho, u stored (48 groups) 249 / 237.
+bool wave_rows(int n) { return n % 64 == 0 || 64 % n == 0; }
 
 void default_block(int nx, int& bx, int& by)
 {
@@ -234,7 +245,7 @@ void default_block(int nx, int& bx, int& by)
     by = std::max(1, 256 / bx);
 }
 
-// Work-group shape of the one-point reverse step: the default shape capped at
+// Work-group shape of the one-point reverse step on rows that fill waves: the default shape capped at
 // the kernel's 256 work-items (rows that are a multiple of 512 points take
 // 512-point groups for the forward steps).
 void adjoint_block(int nx, int& bx, int& by)
@@ -255,12 +266,16 @@ lbmk::Launch adjoint_launch(const d3q19::Dims& dims, bool vec_ok, hipStream_t st
     if (vec) {
         d3q19::Dims q = dims;
         q.nx = dims.nx / 2;
-        const int rbx = std::min(q.nx, 64);
+        q.nxy = (uint32_t)q.nx * (uint32_t)q.ny;
+        q.flat = wave_rows(q.nx) ? 0u : 1u;
+        const int rbx = q.flat ? 64 : std::min(q.nx, 64);
         return lbmk::make_launch(q, rbx, std::max(1, 64 / rbx), stream);
     }
-    int abx, aby;
-    adjoint_block(dims.nx, abx, aby);
-    return lbmk::make_launch(dims, abx, aby, stream);
+    int abx = 256, aby = 1;
+    d3q19::Dims q = dims;
+    q.flat = wave_rows(dims.nx) ? 0u : 1u;
+    if (!q.flat) adjoint_block(dims.nx, abx, aby);
+    return lbmk::make_launch(q, abx, aby, stream);
 }
 
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -376,6 +391,7 @@ namespace {
 // Launch layout of a lattice, resolved from its size and options.
 struct Layout {
     int bx = 0, by = 0;        // one-point kernels
+    bool flat1 = false;        // one-point kernels on a one-dimensional grid per plane
     int cpl = 1;               // points per work-item of the AB step
     int bx4 = 0, by4 = 0;      // vector AB step work-group
     bool flat = false;         // vector AB step on a one-dimensional grid per plane
@@ -395,6 +411,8 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     if (opt.groups_per_cu < -1 || opt.groups_per_cu > 64)
         return fail(LBM_ERR_INVALID, "groups_per_cu must be -1, 0 or 1..64 (got %d)", opt.groups_per_cu);
     int bx = opt.block_x, by = opt.block_y;
+    const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx);
+    if (flat1) { bx = 256; by = 1; }
     if (bx == 0 && by == 0) default_block(nx, bx, by);
     if (bx <= 0 || by <= 0 || bx * by > 1024) return fail(LBM_ERR_INVALID, "bad block shape %dx%d", bx, by);
     if ((ny + by - 1) / by > 65535) return fail(LBM_ERR_INVALID, "ny/block_y must be <= 65535 work-groups");
@@ -414,12 +432,11 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
         if (opt.block_x == 0 && opt.block_y == 0) {
             // one wave per work-group along x (a whole 256-point row when
             // nx = 256 and vw = 4): the fastest shape measured at 256^3 on MI355X.
-            // Rows of more than 64 groups that are not a multiple of 64 (a
-            // 260-point row: 65 groups) take a one-dimensional grid over the
-            // plane instead, which keeps every wave full.
+            // Rows whose groups do not fill waves (a 260-point row: 65 groups)
+            // take a one-dimensional grid over the plane instead.
             bx4 = std::min(nx / vw, 64);
             by4 = std::max(1, 64 / bx4);
-            flat = nx / vw > 64 && (nx / vw) % 64 != 0;
+            flat = !wave_rows(nx / vw);
             cpl = vw;
         } else if (bx * by <= 256) {
             bx4 = bx; by4 = by;
@@ -430,7 +447,7 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
         return fail(LBM_ERR_INVALID, "cells_per_lane = %d needs the AB pattern, nx %% %d == 0 and <= 256 work-items per group",
                     vw, vw);
     if (cpl > 1 && (ny + by4 - 1) / by4 > 65535) return fail(LBM_ERR_INVALID, "ny/block_y must be <= 65535 work-groups");
-    lay.bx = bx; lay.by = by; lay.cpl = cpl; lay.bx4 = bx4; lay.by4 = by4; lay.flat = flat;
+    lay.bx = bx; lay.by = by; lay.flat1 = flat1; lay.cpl = cpl; lay.bx4 = bx4; lay.by4 = by4; lay.flat = flat;
     return LBM_OK;
 }
 
@@ -604,6 +621,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     if (!L) return fail(LBM_ERR_OOM, "host allocation failed");
     L->nx = nx; L->ny = ny; L->nz = nz; L->N = (size_t)N;
     L->dims = dims_of(nx, ny, nz);
+    L->dims.flat = lay.flat1 ? 1u : 0u;
     L->device = dev;
     L->storage = opt.storage;
     L->pattern = opt.pattern;
@@ -1239,6 +1257,9 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
 {
     const lbmk::Launch LA = launch_of(L);
     const lbmk::StepArgs args = step_args(L);
+    lbmk::StepArgs rargs = args;   // the reverse step has a launch shape of its own
+    rargs.d.flat = !vec && !wave_rows(L->nx) ? 1u : 0u;
+    rargs.agx = vec && !wave_rows(L->nx / 2) ? (uint32_t)(L->nx / 2) : 0u;
     const int fm = force_mode(L);
     const float inv_tau2 = (float)(1.0 / ((double)L->tau * (double)L->tau));
     const int T = L->traj_T, K = L->traj_K;
@@ -1265,11 +1286,11 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
         for (int j = len - 1; j >= 0; --j) {
             if (vec)
                 HIPCHK(L, lbmk::launch_adjoint_stepv(2, direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part,
-                                                     L->d_flags, L->d_smask, L->d_mmask, L->d_force, args, inv_tau2,
+                                                     L->d_flags, L->d_smask, L->d_mmask, L->d_force, rargs, inv_tau2,
                                                      LR));
             else
                 HIPCHK(L, lbmk::launch_adjoint_step(direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part, L->d_flags,
-                                                    L->d_force, args, inv_tau2, LR));
+                                                    L->d_force, rargs, inv_tau2, LR));
             ab ^= 1;
             direct = false;
         }
