@@ -356,16 +356,20 @@ __global__ __launch_bounds__(256) void k_zero_f64(double* __restrict__ p, size_t
     if (k < n) p[k] = 0.0;
 }
 
-// out[0] = p[0] + p[1] + ... + p[n-1], added one by one in index order by a
-// single work-item: the order and rounding of the host loop that sums the
-// per-work-group tau partials, so both give the same bits.
-__global__ __launch_bounds__(64) void k_sum_f64_ordered(const double* __restrict__ p, size_t n,
-                                                        double* __restrict__ out)
+// out[0] = sum of p[0..n) by one work-group, in an order that depends on n
+// alone; out may be p.
+__global__ __launch_bounds__(1024) void k_sum_f64(const double* p, size_t n, double* out)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ double part[1024];
     double s = 0.0;
-    for (size_t k = 0; k < n; ++k) s += p[k];
-    out[0] = s;
+    for (size_t k = threadIdx.x; k < n; k += 1024) s += p[k];
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (unsigned span = 512; span > 0; span >>= 1) {
+        if (threadIdx.x < span) part[threadIdx.x] += part[threadIdx.x + span];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[0] = part[0];
 }
 
 hipError_t launch_zero_f64(double* p, size_t n, hipStream_t s)
@@ -375,9 +379,9 @@ hipError_t launch_zero_f64(double* p, size_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_sum_f64_ordered(const double* p, size_t n, double* out, hipStream_t s)
+hipError_t launch_sum_f64(const double* p, size_t n, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sum_f64_ordered, dim3(1), dim3(64), 0, s, p, n, out);
+    hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(1024), 0, s, p, n, out);
     return hipGetLastError();
 }
 

@@ -102,6 +102,7 @@ struct lbm_lattice {
     long long version = 0;           // bumped by anything that changes the dynamics/state
     float* d_seg = nullptr;          // (K-1) states
     int seg_cap = 0;
+    int seg_of = -1;                 // segment whose states d_seg holds (-1: none)
     void* traj_dev = nullptr;        // caller-owned checkpoint store (NULL: library allocates)
     size_t traj_bytes = 0;
     bool traj_owned = true;          // ckpt / d_seg were allocated by the library
@@ -326,8 +327,56 @@ void drop_trajectory(lbm_lattice* L)
     L->ckpt.clear();
     L->d_seg = nullptr;
     L->seg_cap = 0;
+    L->seg_of = -1;
     L->traj_T = -1;
     L->traj_version = -1;
+}
+
+// Checkpoint store of nck states and nseg segment states. What the last
+// rollout allocated is used again: surplus is given back first, only the
+// shortfall is allocated (a 256^3 store of 7 states took 80 ms to free and
+// allocate again, more than twice the rollout and its adjoint).
+lbm_status hold_trajectory(lbm_lattice* L, int nck, int nseg)
+{
+    const size_t sb = state_bytes_of(L->N);
+    L->traj_T = -1;
+    L->traj_version = -1;
+    L->seg_of = -1;
+    if (L->traj_dev) {
+        // caller store: checkpoints at 256-byte-aligned state slots, then the
+        // segment states back to back
+        drop_trajectory(L);
+        L->traj_owned = false;
+        char* base = static_cast<char*>(L->traj_dev);
+        const size_t sbr = round256(sb);
+        for (int k = 0; k < nck; ++k) L->ckpt.push_back(reinterpret_cast<float*>(base + (size_t)k * sbr));
+        if (nseg > 0) L->d_seg = reinterpret_cast<float*>(base + (size_t)nck * sbr);
+        L->seg_cap = nseg;
+        return LBM_OK;
+    }
+    if (!L->traj_owned) drop_trajectory(L);
+    L->traj_owned = true;
+    while ((int)L->ckpt.size() > nck) {
+        dfree(L, L->ckpt.back(), sb);
+        L->ckpt.pop_back();
+    }
+    if (L->seg_cap != nseg) {
+        dfree(L, L->d_seg, sb * (size_t)L->seg_cap);
+        L->d_seg = nullptr;
+        L->seg_cap = 0;
+    }
+    lbm_status st = LBM_OK;
+    while ((int)L->ckpt.size() < nck && st == LBM_OK) {
+        float* p = nullptr;
+        st = dalloc(L, &p, sb, "checkpoint");
+        if (st == LBM_OK) L->ckpt.push_back(p);
+    }
+    if (st == LBM_OK && nseg > 0 && !L->d_seg) {
+        st = dalloc(L, &L->d_seg, sb * (size_t)nseg, "segment store");
+        if (st == LBM_OK) L->seg_cap = nseg;
+    }
+    if (st != LBM_OK) drop_trajectory(L);
+    return st;
 }
 
 // Releases library-allocated adjoint buffers; caller workspace pointers are
@@ -347,7 +396,8 @@ void drop_adjoint_buffers(lbm_lattice* L)
 
 void invalidate(lbm_lattice* L) { ++L->version; }
 
-lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho = nullptr, float* u = nullptr);
+lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho = nullptr, float* u = nullptr,
+                     void* from = nullptr, void* to = nullptr);
 lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2], double* part,
                          const lbmk::Launch& LR, bool vec);
 
@@ -1076,42 +1126,38 @@ lbm_status lbm_forward_checkpointed(lbm_lattice* L, int T, int K)
         return fail(LBM_ERR_INVALID, "the trajectory buffer holds %zu bytes; T = %d, K = %d needs %zu", L->traj_bytes,
                     T, K, need);
     DeviceGuard guard(L->device);
-    drop_trajectory(L);
-    const size_t sb = (size_t)Q * L->N * sizeof(float);
     const int nck = T == 0 ? 1 : (T + K - 1) / K;
-    const int segK = std::min(K, std::max(T, 1));
-    if (L->traj_dev) {
-        // caller store: checkpoints at 256-byte-aligned state slots, then the
-        // segment states back to back
-        L->traj_owned = false;
-        char* base = static_cast<char*>(L->traj_dev);
-        const size_t sbr = round256(sb);
-        for (int k = 0; k < nck; ++k) L->ckpt.push_back(reinterpret_cast<float*>(base + (size_t)k * sbr));
-        if (segK > 1) {
-            L->d_seg = reinterpret_cast<float*>(base + (size_t)nck * sbr);
-            L->seg_cap = segK - 1;
-        }
-    } else {
-        L->traj_owned = true;
-        for (int k = 0; k < nck; ++k) {
-            float* p = nullptr;
-            st = dalloc(L, &p, sb, "checkpoint");
-            if (st != LBM_OK) { drop_trajectory(L); return st; }
-            L->ckpt.push_back(p);
-        }
-        if (segK > 1) {
-            st = dalloc(L, &L->d_seg, sb * (size_t)(segK - 1), "segment store");
-            if (st != LBM_OK) { drop_trajectory(L); return st; }
-            L->seg_cap = segK - 1;
-        }
-    }
-    for (int k = 0; k < nck; ++k) {
-        HIPCHK(L, hipMemcpyAsync(L->ckpt[k], L->d_f[L->cur], sb, hipMemcpyDeviceToDevice, L->stream));
+    st = hold_trajectory(L, nck, std::min(K, std::max(T, 1)) - 1);
+    if (st != LBM_OK) return st;
+    // Only the first checkpoint is a copy: the last step of a segment stores
+    // its state where the next checkpoint belongs, and the next step reads it
+    // there. (Finite checks look at the lattice's own arrays, so with them
+    // every checkpoint is copied.) The states inside the last segment go into
+    // the segment store, where the reverse sweep wants them first.
+    const bool copies = L->check_interval > 0;
+    const size_t floats = (size_t)Q * L->N;
+    for (int k = 0; k < nck && st == LBM_OK; ++k) {
+        void* from = nullptr;
+        if (k == 0 || copies)
+            HIPCHK(L, lbmk::launch_copy(static_cast<const float*>(L->d_f[L->cur]), L->ckpt[k], floats, L->stream));
+        else
+            from = L->ckpt[k];
         const int len = std::min(K, T - k * K);
-        if (len > 0) {
-            st = run_steps(L, len, true);
-            if (st != LBM_OK) { drop_trajectory(L); return st; }
+        if (len <= 0) break;
+        if (k + 1 < nck || copies) {
+            st = run_steps(L, len, true, nullptr, nullptr, from, copies ? nullptr : L->ckpt[k + 1]);
+            continue;
         }
+        for (int j = 0; j < len && st == LBM_OK; ++j) {
+            float* to = j + 1 < len ? L->d_seg + (size_t)j * floats : nullptr;
+            st = run_steps(L, 1, true, nullptr, nullptr, from, to);
+            from = to;
+        }
+        L->seg_of = k;
+    }
+    if (st != LBM_OK) {
+        drop_trajectory(L);
+        return st;
     }
     L->traj_T = T;
     L->traj_K = K;
@@ -1150,11 +1196,10 @@ lbm_status lbm_adjoint(lbm_lattice* L, const float* g, float* gF, double* grad_t
     float* adj[2] = {L->d_adj[0], L->d_adj[1]};
     st = adjoint_sweep(L, g, gF, adj, L->d_taupart, LR, vec);
     if (st != LBM_OK) return st;
-    std::vector<double> parts(nblk);
-    HIPCHK(L, hipMemcpyAsync(parts.data(), L->d_taupart, nblk * sizeof(double), hipMemcpyDeviceToHost, L->stream));
-    HIPCHK(L, hipStreamSynchronize(L->stream));
+    HIPCHK(L, lbmk::launch_sum_f64(L->d_taupart, nblk, L->d_taupart, L->stream));
     double s = 0.0;
-    for (double v : parts) s += v;
+    HIPCHK(L, hipMemcpyAsync(&s, L->d_taupart, sizeof(double), hipMemcpyDeviceToHost, L->stream));
+    HIPCHK(L, hipStreamSynchronize(L->stream));
     *grad_tau = s;
     return LBM_OK;
 }
@@ -1237,7 +1282,7 @@ lbm_status lbm_adjoint_noalloc(lbm_lattice* L, const float* g, float* gF, double
     HIPCHK(L, lbmk::launch_zero_f64(part, nblk, L->stream));
     st = adjoint_sweep(L, g, gF, adj, part, LR, vec);
     if (st != LBM_OK) return st;
-    HIPCHK(L, lbmk::launch_sum_f64_ordered(part, nblk, sum, L->stream));
+    HIPCHK(L, lbmk::launch_sum_f64(part, nblk, sum, L->stream));
     double h = 0.0;
     HIPCHK(L, hipMemcpyAsync(&h, sum, sizeof(double), hipMemcpyDeviceToHost, L->stream));
     HIPCHK(L, hipStreamSynchronize(L->stream));
@@ -1273,9 +1318,10 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
     for (int k = nck - 1; k >= 0 && T > 0; --k) {
         const int t0 = k * K;
         const int len = std::min(K, T - t0);
-        // recompute s^{t0+1} .. s^{t0+len-1} into the segment store
+        // recompute s^{t0+1} .. s^{t0+len-1} into the segment store, unless it
+        // holds them (the rollout's last segment)
         auto state = [&](int j) -> float* { return j == 0 ? L->ckpt[k] : L->d_seg + (size_t)(j - 1) * Q * L->N; };
-        for (int j = 1; j < len; ++j) {
+        for (int j = 1; j < len && L->seg_of != k; ++j) {
             if (L->cpl > 1)
                 HIPCHK(L, lbmk::launch_step_abv(LBM_STORAGE_F32, L->cpl, true, fm, state(j - 1), state(j), L->d_flags,
                                                 L->d_smask, L->d_mmask, L->d_force, args, launch4_of(L)));
@@ -1283,6 +1329,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
                 HIPCHK(L, lbmk::launch_step(LBM_STORAGE_F32, LBM_PATTERN_AB, 0, true, fm, state(j - 1), state(j),
                                             L->d_flags, L->d_smask, L->d_mmask, L->d_force, args, LA));
         }
+        L->seg_of = k;
         for (int j = len - 1; j >= 0; --j) {
             if (vec)
                 HIPCHK(L, lbmk::launch_adjoint_stepv(2, direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part,
@@ -1299,8 +1346,10 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
 }
 
 // n steps; with rho/u (AB pattern) the last step also stores its in-step
-// rho and u.
-lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u)
+// rho and u. AB pattern only: `from` (else the lattice's current array) holds
+// the state, `to` (else the lattice's other array) receives the last step's;
+// after a call with `to` the next one has to start `from` there.
+lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, void* from, void* to)
 {
     if (n == 0) return LBM_OK;
     const lbmk::StepArgs args = step_args(L);
@@ -1313,14 +1362,16 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u)
         L->ev_recorded = 1;
     }
     const bool pairs = collide && takes_pairs(L);
+    // arrays of the launch whose first step is s / whose last step is s
+    auto in = [&](int s) { return s == 0 && from ? from : L->d_f[L->cur]; };
+    auto out = [&](int s) { return s == n - 1 && to ? to : L->d_f[L->cur ^ 1]; };
     for (int s = 0; s < n; ++s) {
         // two steps in one launch, unless the second is the one that stores
         // rho and u or a finite check is due in between
         if (pairs && n - s >= 2 && !(rho && n - s == 2) &&
             (L->check_interval == 0 || (L->steps_done + 1) % L->check_interval != 0)) {
-            HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags, L->d_smask,
-                                             L->d_mmask, L->d_force, args, L->pair_shape, L->walls, L->moving,
-                                             L->stream));
+            HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
+                                             L->d_force, args, L->pair_shape, L->walls, L->moving, L->stream));
             L->cur ^= 1;
             L->steps_done += 2;
             ++s;
@@ -1333,11 +1384,11 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u)
         float* mr = s == n - 1 ? rho : nullptr;
         float* mu = s == n - 1 ? u : nullptr;
         if (L->pattern == LBM_PATTERN_AB && L->cpl > 1) {
-            HIPCHK(L, lbmk::launch_step_abv(L->storage, vec_shape(L).cpl, collide, fm, L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags,
+            HIPCHK(L, lbmk::launch_step_abv(L->storage, vec_shape(L).cpl, collide, fm, in(s), out(s), L->d_flags,
                                             L->d_smask, L->d_mmask, L->d_force, args, LA4, mr, mu, L->onsite));
             L->cur ^= 1;
         } else if (L->pattern == LBM_PATTERN_AB) {
-            HIPCHK(L, lbmk::launch_step(L->storage, 0, 0, collide, fm, L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags,
+            HIPCHK(L, lbmk::launch_step(L->storage, 0, 0, collide, fm, in(s), out(s), L->d_flags,
                                         L->d_smask, L->d_mmask, L->d_force, args, LA, mr, mu, L->onsite));
             L->cur ^= 1;
         } else {

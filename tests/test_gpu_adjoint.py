@@ -309,3 +309,42 @@ def test_autograd_force_shapes():
         rollout(lat, torch.zeros(3, device="cuda", requires_grad=True),
                 torch.tensor(tau, dtype=torch.float64), T=2, K=1, s0=s0_t)
     lat.close()
+
+
+def test_rollouts_reuse_the_checkpoint_store():
+    """Rollouts of different lengths on one lattice, each followed by two
+    sweeps, against a fresh lattice each: the kept store and the states that
+    the rollout leaves in it change nothing, and the store is as large as the
+    last rollout needs. With a finite check the checkpoints are copied."""
+    from paper_1309_1983_amd import Lattice
+    shape = (20, 13, 9)
+    N = int(np.prod(shape))
+    flags = W.random_flags(N, 31, 0.15, 0.05)
+    F = torch.from_numpy(W.random_force_field(N, 32, 1e-3).astype(np.float32))
+    s0 = torch.from_numpy(near_rest_state(N, 33))
+    g = torch.from_numpy(W.random_velocity(N, 34, 1.0).astype(np.float32)).cuda()
+
+    def lattice(**kw):
+        lat = Lattice(*shape, 0.7, flags=flags, **kw)
+        lat.set_wall_velocity(0.03, -0.01, 0.02)
+        lat.set_force(F)
+        return lat
+
+    def sweep(lat, T, K):
+        lat.set_populations(s0)
+        lat.forward_checkpointed(T, K)
+        u = lat.macros()[1]
+        return (u, *lat.adjoint(g), *lat.adjoint(g))
+
+    kept, checked = lattice(), lattice(check_interval=2)
+    for T, K in ((12, 5), (7, 7), (1, 1), (9, 1), (12, 5), (0, 3)):
+        fresh = lattice()
+        ref = sweep(fresh, T, K)
+        for lat in (kept, checked):
+            got = sweep(lat, T, K)
+            for a, b in zip(got, ref):
+                assert torch.equal(a, b) if torch.is_tensor(a) else a == b, (T, K)
+        assert kept.device_bytes() == fresh.device_bytes(), (T, K)
+        fresh.close()
+    kept.close()
+    checked.close()
