@@ -169,6 +169,14 @@ __device__ __forceinline__ void stv_nt(B* base, uint32_t idx, typename Vec<B, VW
     }
 }
 
+// The same for one element, as a global store (16-bit raw buffer stores were
+// 4% slower on the sphere duct).
+template <class T>
+__device__ __forceinline__ void st_nt(T* base, uint32_t idx, T v)
+{
+    __builtin_nontemporal_store(v, reinterpret_cast<T*>(reinterpret_cast<char*>(base) + idx * (uint32_t)sizeof(T)));
+}
+
 template <class B>
 __device__ __forceinline__ typename V4<B>::t ld4(const B* base, uint32_t idx) { return ldv<4>(base, idx); }
 

@@ -21,6 +21,7 @@ struct StepArgs {
                                 // the gx * ny point groups of a z-plane (gx = nx / vw groups
                                 // per row, x fastest); 0 = two-dimensional (x groups, y)
     uint32_t agx;               // the same for the vector reverse step: groups per row, 0 = two-dimensional
+    uint32_t stream;            // one-point AB step: store with the non-temporal hint
     uint32_t early;             // FP32 vector AB step: issue the gather before the flag
                                 // branches (porous geometry)
 };
@@ -63,6 +64,7 @@ struct PairShape {
     uint32_t tx, rows, depth;
     uint32_t ntx, nty, groups;   // tiles in x and y, work-groups in all
     uint32_t threads;
+    uint32_t stream;             // store with the non-temporal hint
 };
 // `a` holds the state, `b` receives the state two steps later. walls: the
 // lattice has solid points (FP32 storage only); moving: some of them move.

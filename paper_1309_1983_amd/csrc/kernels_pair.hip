@@ -58,25 +58,25 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v)
                       __builtin_amdgcn_readlane((int)v, 47) | __builtin_amdgcn_readlane((int)v, 63));
 }
 
-// Non-temporal store of one element; an offset of PAIR_DROP lies outside the
+// Store of one element (HINT 2: non-temporal); an offset of PAIR_DROP lies outside the
 // resource and is discarded by the range check, so that every work-item
 // issues the same stores (a branch around them would make the compiler wait
 // for them before the next plane's loads are used).
 constexpr uint32_t PAIR_DROP = 0xfffffff0u;
-template <class B>
+template <int HINT, class B>
 __device__ __forceinline__ void store_or_drop(B v, B* base, uint32_t bytes, uint32_t off)
 {
     const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)bytes, 0x00020000);
     if constexpr (sizeof(B) == 4)
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 2);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, HINT);
     else
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, 0, 2);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, off, 0, HINT);
 }
 
 // The march of one (x, y) column along the planes z0 .. z0 + depth - 1.
 // OUT: the wave holds output points; the others only provide s^{t+1} of the
 // halo, and take the same barriers.
-template <class St, int FM, bool WALLS, bool MOVING, bool OUT>
+template <class St, int FM, bool WALLS, bool MOVING, bool STREAM, bool OUT>
 __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict__ src,
                                            typename St::bits_t* __restrict__ dst, const uint8_t* __restrict__ flags,
                                            const uint32_t* __restrict__ smask, const uint32_t* __restrict__ mmask,
@@ -243,7 +243,8 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
             const uint32_t zo = (uint32_t)max(zt - 1, 0);
 #pragma unroll
             for (int i = 0; i < Q; ++i)
-                store_or_drop<B>(St::enc_b(h[i], i), plane(dst, d, i, zo), d.nxy * (uint32_t)sizeof(B), off);
+                store_or_drop<STREAM ? 2 : 0>(St::enc_b(h[i], i), plane(dst, d, i, zo), d.nxy * (uint32_t)sizeof(B),
+                                              off);
             // gathers of plane zt for the output planes zt and zt + 1
             q[0] = e[0];
             q[5] = up[5];
@@ -275,7 +276,7 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
 
 }  // namespace
 
-template <class St, int FM, bool WALLS, bool MOVING>
+template <class St, int FM, bool WALLS, bool MOVING, bool STREAM>
 __global__ __launch_bounds__(NT, NT / 256) void k_step_pair(const typename St::bits_t* __restrict__ src,
                                                             typename St::bits_t* __restrict__ dst,
                                                             const uint8_t* __restrict__ flags,
@@ -315,23 +316,31 @@ __global__ __launch_bounds__(NT, NT / 256) void k_step_pair(const typename St::b
     x = x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x);
     y = y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y);
     if (!WALLS || __builtin_amdgcn_ballot_w64(out) != 0ull)
-        pair_march<St, FM, WALLS, MOVING, true>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
+        pair_march<St, FM, WALLS, MOVING, STREAM, true>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
     else
-        pair_march<St, FM, WALLS, MOVING, false>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
+        pair_march<St, FM, WALLS, MOVING, STREAM, false>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
+}
+
+template <class St, int FM, bool WALLS, bool MOVING, bool STREAM>
+static hipError_t pair_stream(const void* a, void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
+                              const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
+{
+    using B = typename St::bits_t;
+    if (name) {
+        *name = reinterpret_cast<const void*>(&k_step_pair<St, FM, WALLS, MOVING, STREAM>);
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((k_step_pair<St, FM, WALLS, MOVING, STREAM>), dim3((ps.groups + 7u) / 8u * 8u), dim3(ps.threads), 0,
+                       s, static_cast<const B*>(a), static_cast<B*>(b), flags, sm, mm, ff, args, ps);
+    return hipGetLastError();
 }
 
 template <class St, int FM, bool WALLS, bool MOVING>
 static hipError_t pair_launch(const void* a, void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
                               const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
 {
-    using B = typename St::bits_t;
-    if (name) {
-        *name = reinterpret_cast<const void*>(&k_step_pair<St, FM, WALLS, MOVING>);
-        return hipSuccess;
-    }
-    hipLaunchKernelGGL((k_step_pair<St, FM, WALLS, MOVING>), dim3((ps.groups + 7u) / 8u * 8u), dim3(ps.threads), 0, s,
-                       static_cast<const B*>(a), static_cast<B*>(b), flags, sm, mm, ff, args, ps);
-    return hipGetLastError();
+    return ps.stream ? pair_stream<St, FM, WALLS, MOVING, true>(a, b, flags, sm, mm, ff, args, ps, s, name)
+                     : pair_stream<St, FM, WALLS, MOVING, false>(a, b, flags, sm, mm, ff, args, ps, s, name);
 }
 
 template <class St, bool WALLS, bool MOVING>
@@ -339,7 +348,10 @@ static hipError_t pair_fm(int fm, const void* a, void* b, const uint8_t* flags, 
                           const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
 {
     switch (fm) {
-    case FORCE_UNIFORM: return pair_launch<St, FORCE_UNIFORM, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
+    case FORCE_UNIFORM:   // FP32 only
+        if constexpr (sizeof(typename St::bits_t) == 4)
+            return pair_launch<St, FORCE_UNIFORM, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
+        return hipErrorInvalidValue;
     case FORCE_FIELD: return pair_launch<St, FORCE_FIELD, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
     default: return pair_launch<St, FORCE_NONE, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
     }

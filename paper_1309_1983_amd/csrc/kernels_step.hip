@@ -10,7 +10,7 @@
 // work-groups stream through a compact address window.
 #include <type_traits>
 
-#include "kernels.hpp"
+#include "step_common.hpp"
 
 using namespace d3q19;
 
@@ -29,113 +29,6 @@ Launch make_launch(const Dims& d, int bx, int by, hipStream_t s)
     L.grid = dim3((unsigned)((d.nx + bx - 1) / bx), (unsigned)((d.ny + by - 1) / by), (unsigned)d.nz);
     L.stream = s;
     return L;
-}
-
-template <int FM>
-__device__ __forceinline__ void load_force(const StepArgs& a, const float* __restrict__ ff, uint32_t c,
-                                           float& Fx, float& Fy, float& Fz)
-{
-    if (FM == FORCE_UNIFORM) {
-        Fx = a.Fx; Fy = a.Fy; Fz = a.Fz;
-    } else if (FM == FORCE_FIELD) {
-        Fx = ff[c];
-        Fy = ff[(size_t)a.d.N + c];
-        Fz = ff[2 * (size_t)a.d.N + c];
-    } else {
-        Fx = Fy = Fz = 0.0f;
-    }
-}
-
-// Decode, add moving-wall terms, rebuild the unknowns of an on-site node
-// (onsiteU != 0: its solid-source directions), collide. h ends as
-// post-collision offsets.
-template <class St, int FM, bool ONSITE>
-__device__ __forceinline__ Macro decode_collide(const typename St::raw_t raw[Q], uint32_t mwmask,
-                                                uint32_t onsiteU, bool onsite_moving,
-                                                const StepArgs& a, const float* __restrict__ ff,
-                                                uint32_t c, float h[Q])
-{
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        h[i] = St::off(raw[i], i);
-        if (i > 0 && ((mwmask >> i) & 1u)) h[i] = h[i] + a.mw[i];
-    }
-    float Fx, Fy, Fz;
-    load_force<FM>(a, ff, c, Fx, Fy, Fz);
-    if (ONSITE && onsiteU) {
-        const float ux = onsite_moving ? a.uw[0] : 0.0f;
-        const float uy = onsite_moving ? a.uw[1] : 0.0f;
-        const float uz = onsite_moving ? a.uw[2] : 0.0f;
-        onsite_rebuild<FM != FORCE_NONE>(h, onsiteU, ux, uy, uz, Fx, Fy, Fz);
-    }
-    return bgk_collide<FM != FORCE_NONE>(h, a.omega, a.cF, Fx, Fy, Fz);
-}
-
-#define POINT_PROLOGUE(d)                                                                      \
-    int x, y;                                                                                  \
-    if (!point_of((d), x, y)) return;                                                          \
-    const uint32_t z = blockIdx.z;                                                             \
-    const uint32_t o = (uint32_t)y * (uint32_t)(d).nx + (uint32_t)x;                           \
-    const uint32_t c = z * (d).nxy + o;                                                        \
-    const uint32_t zm = wrap_m(z, (uint32_t)(d).nz), zp = wrap_p(z, (uint32_t)(d).nz);
-
-// ---------------------------------------------------------------------------
-// AB pull step, one point per work-item: gather from x - e_i in `src`,
-// bounce back at solid neighbours, collide, store into `dst`. Used when the
-// row length is not a multiple of the vector width. MACROS: also store the
-// in-step rho and u (the four extra stores per point of Section 4.1).
-// ONSITE: rebuild the unknown populations of on-site velocity nodes.
-// ---------------------------------------------------------------------------
-template <class St, int FM, bool COLLIDE, bool MACROS, bool ONSITE>
-__global__ __launch_bounds__(1024) void k_step_ab(const typename St::raw_t* __restrict__ src,
-                                                  typename St::raw_t* __restrict__ dst,
-                                                  const uint8_t* __restrict__ flags,
-                                                  const uint32_t* __restrict__ smask,
-                                                  const uint32_t* __restrict__ mmask,
-                                                  const float* __restrict__ ff, StepArgs a,
-                                                  float* __restrict__ rho_out, float* __restrict__ u_out)
-{
-    using T = typename St::raw_t;
-    const Dims& d = a.d;
-    POINT_PROLOGUE(d)
-    const uint8_t fl = flags[c];
-    if (fl & TYPE_MASK) {
-        if (MACROS) {
-            rho_out[c] = 0.0f;
-            u_out[c] = 0.0f; u_out[(size_t)d.N + c] = 0.0f; u_out[2 * (size_t)d.N + c] = 0.0f;
-        }
-        return;
-    }
-
-    uint32_t on[Q];
-    pull_offsets(d, x, y, on);
-    T raw[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) raw[i] = ld(plane(src, d, i, src_slab(i, z, zm, zp)), on[i]);
-
-    uint32_t mwmask = 0, solid = 0;
-    if (fl & NEAR_WALL) {
-        solid = smask[c];
-        if (fl & NEAR_MOVING) mwmask = mmask[c];
-#pragma unroll
-        for (int i = 1; i < Q; ++i)
-            if ((solid >> i) & 1u) raw[i] = ld(plane(src, d, OPP[i], z), o);
-    }
-
-    if (!COLLIDE) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) st(plane(dst, d, i, z), o, raw[i]);
-        return;
-    }
-    float h[Q];
-    const Macro m = decode_collide<St, FM, ONSITE>(raw, mwmask, (fl & ONSITE_NODE) ? solid : 0u,
-                                                   (fl & ONSITE_MOVING) != 0, a, ff, c, h);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) st(plane(dst, d, i, z), o, St::enc(h[i], i));
-    if (MACROS) {
-        rho_out[c] = m.rho;
-        u_out[c] = m.ux; u_out[(size_t)d.N + c] = m.uy; u_out[2 * (size_t)d.N + c] = m.uz;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -383,90 +276,6 @@ void k_step_abv(const typename St::bits_t* __restrict__ src,
 }
 
 // ---------------------------------------------------------------------------
-// AA pattern, one array, in place.
-// Parity 0 (array holds s_i(x) at slot [i][x]): read p_i from [i][x - e_i],
-// or from [opp(i)][x] when x - e_i is solid; write s'_j into the slot that
-// p_opp(j) was read from. Afterwards s'_j(x) sits at [opp(j)][x + e_j]
-// (or at [j][x] when x + e_j is solid).
-// Parity 1: p_i = [opp(i)][x] for every i (local); write s'_i to [i][x],
-// restoring the natural layout. Each work-item reads and writes the same 19
-// slots, and no two work-items share a slot, so the update is race-free.
-// ---------------------------------------------------------------------------
-template <class St, int FM, bool COLLIDE, bool ONSITE>
-__global__ __launch_bounds__(1024) void k_step_aa0(typename St::raw_t* f,
-                                                   const uint8_t* __restrict__ flags,
-                                                   const uint32_t* __restrict__ smask,
-                                                   const uint32_t* __restrict__ mmask,
-                                                   const float* __restrict__ ff, StepArgs a)
-{
-    using T = typename St::raw_t;
-    const Dims& d = a.d;
-    POINT_PROLOGUE(d)
-    const uint8_t fl = flags[c];
-    if (fl & TYPE_MASK) return;
-
-    uint32_t on[Q];
-    pull_offsets(d, x, y, on);
-    T raw[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) raw[i] = ld(plane(f, d, i, src_slab(i, z, zm, zp)), on[i]);
-
-    uint32_t solid = 0, mwmask = 0;
-    if (fl & NEAR_WALL) {
-        solid = smask[c];
-        if (fl & NEAR_MOVING) mwmask = mmask[c];
-#pragma unroll
-        for (int i = 1; i < Q; ++i)
-            if ((solid >> i) & 1u) raw[i] = ld(plane(f, d, OPP[i], z), o);
-    }
-
-    float h[Q];
-    if (COLLIDE)
-        decode_collide<St, FM, ONSITE>(raw, mwmask, (fl & ONSITE_NODE) ? solid : 0u, (fl & ONSITE_MOVING) != 0,
-                                       a, ff, c, h);
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-        const int k = OPP[j];
-        const T v = COLLIDE ? St::enc(h[j], j) : raw[j];
-        if ((solid >> k) & 1u) st(plane(f, d, j, z), o, v);
-        else st(plane(f, d, k, src_slab(k, z, zm, zp)), on[k], v);
-    }
-}
-
-template <class St, int FM, bool COLLIDE, bool ONSITE>
-__global__ __launch_bounds__(1024) void k_step_aa1(typename St::raw_t* f,
-                                                   const uint8_t* __restrict__ flags,
-                                                   const uint32_t* __restrict__ smask,
-                                                   const uint32_t* __restrict__ mmask,
-                                                   const float* __restrict__ ff, StepArgs a)
-{
-    using T = typename St::raw_t;
-    const Dims& d = a.d;
-    POINT_PROLOGUE(d)
-    (void)zm; (void)zp;   // every access of the local step is in the point's own slab
-    const uint8_t fl = flags[c];
-    if (fl & TYPE_MASK) return;
-
-    T raw[Q];
-#pragma unroll
-    for (int i = 0; i < Q; ++i) raw[i] = ld(plane(f, d, OPP[i], z), o);
-
-    uint32_t mwmask = 0, solid = 0;
-    if (COLLIDE && (fl & NEAR_MOVING)) mwmask = mmask[c];
-    if (COLLIDE && ONSITE && (fl & ONSITE_NODE)) solid = smask[c];
-    if (!COLLIDE) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) st(plane(f, d, i, z), o, raw[i]);
-        return;
-    }
-    float h[Q];
-    decode_collide<St, FM, ONSITE>(raw, mwmask, (fl & ONSITE_NODE) ? solid : 0u, (fl & ONSITE_MOVING) != 0, a,
-                                   ff, c, h);
-#pragma unroll
-    for (int i = 0; i < Q; ++i) st(plane(f, d, i, z), o, St::enc(h[i], i));
-}
-
-// ---------------------------------------------------------------------------
 // Stored state of one point in natural order (s_j(x), j = 0..18), for either
 // layout. Layout 1 (AA after an odd number of steps): s_j(x) is at
 // [opp(j)][x + e_j] when x + e_j is fluid, else at [j][x].
@@ -651,77 +460,7 @@ __global__ __launch_bounds__(256) void k_copy(const float* __restrict__ src, flo
 
 // ------------------------------- dispatch ----------------------------------
 
-// While t_resolve is set (resolve_step_kernel), the step dispatch records the
-// kernel it would launch instead of launching it.
-static thread_local const void** t_resolve = nullptr;
-#define STEP_LAUNCH(K, GRID, BLOCK, SHMEM, STREAM, ...)                         \
-    do {                                                                      \
-        if (t_resolve) *t_resolve = reinterpret_cast<const void*>(&K);        \
-        else hipLaunchKernelGGL(K, GRID, BLOCK, SHMEM, STREAM, __VA_ARGS__);  \
-    } while (0)
-
-template <class St, int FM, bool ONSITE>
-static hipError_t step_fm(int pattern, int parity, bool collide, void* a, void* b,
-                          const uint8_t* flags, const uint32_t* sm, const uint32_t* mm, const float* ff,
-                          const StepArgs& args, const Launch& L, float* rho, float* u)
-{
-    using T = typename St::raw_t;
-    T* A = static_cast<T*>(a);
-    T* B = static_cast<T*>(b);
-    if (pattern == 0) {
-        if (collide && rho)
-            STEP_LAUNCH((k_step_ab<St, FM, true, true, ONSITE>), L.grid, L.block, L.shmem, L.stream, A, B, flags, sm, mm, ff, args, rho, u);
-        else if (collide)
-            STEP_LAUNCH((k_step_ab<St, FM, true, false, ONSITE>), L.grid, L.block, L.shmem, L.stream, A, B, flags, sm, mm, ff, args, rho, u);
-        else
-            STEP_LAUNCH((k_step_ab<St, FORCE_NONE, false, false, false>), L.grid, L.block, L.shmem, L.stream, A, B, flags, sm, mm, ff, args, rho, u);
-    } else if (parity == 0) {
-        if (collide)
-            STEP_LAUNCH((k_step_aa0<St, FM, true, ONSITE>), L.grid, L.block, L.shmem, L.stream, A, flags, sm, mm, ff, args);
-        else
-            STEP_LAUNCH((k_step_aa0<St, FORCE_NONE, false, false>), L.grid, L.block, L.shmem, L.stream, A, flags, sm, mm, ff, args);
-    } else {
-        if (collide)
-            STEP_LAUNCH((k_step_aa1<St, FM, true, ONSITE>), L.grid, L.block, L.shmem, L.stream, A, flags, sm, mm, ff, args);
-        else
-            STEP_LAUNCH((k_step_aa1<St, FORCE_NONE, false, false>), L.grid, L.block, L.shmem, L.stream, A, flags, sm, mm, ff, args);
-    }
-    return hipGetLastError();
-}
-
-template <class St, bool ONSITE>
-static hipError_t step_st(int pattern, int parity, bool collide, int fm, void* a, void* b,
-                          const uint8_t* flags, const uint32_t* sm, const uint32_t* mm, const float* ff,
-                          const StepArgs& args, const Launch& L, float* rho, float* u)
-{
-    switch (fm) {
-    case FORCE_UNIFORM: return step_fm<St, FORCE_UNIFORM, ONSITE>(pattern, parity, collide, a, b, flags, sm, mm, ff, args, L, rho, u);
-    case FORCE_FIELD: return step_fm<St, FORCE_FIELD, ONSITE>(pattern, parity, collide, a, b, flags, sm, mm, ff, args, L, rho, u);
-    default: return step_fm<St, FORCE_NONE, ONSITE>(pattern, parity, collide, a, b, flags, sm, mm, ff, args, L, rho, u);
-    }
-}
-
-template <bool ONSITE>
-static hipError_t step_os(int storage, int pattern, int parity, bool collide, int force_mode, void* a,
-                          void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
-                          const float* ffield, const StepArgs& args, const Launch& L, float* rho, float* u)
-{
-    switch (storage) {
-    case 1: return step_st<StF16, ONSITE>(pattern, parity, collide, force_mode, a, b, flags, sm, mm, ffield, args, L, rho, u);
-    case 2: return step_st<StBF16, ONSITE>(pattern, parity, collide, force_mode, a, b, flags, sm, mm, ffield, args, L, rho, u);
-    default: return step_st<StF32, ONSITE>(pattern, parity, collide, force_mode, a, b, flags, sm, mm, ffield, args, L, rho, u);
-    }
-}
-
-hipError_t launch_step(int storage, int pattern, int parity, bool collide, int force_mode, void* a,
-                       void* b, const uint8_t* flags, const uint32_t* smask, const uint32_t* mmask,
-                       const float* ffield, const StepArgs& args, const Launch& L, float* rho, float* u,
-                       bool onsite)
-{
-    return (onsite && collide)
-               ? step_os<true>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, args, L, rho, u)
-               : step_os<false>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, args, L, rho, u);
-}
+thread_local const void** t_resolve = nullptr;
 
 template <class St, int FM, int VW, bool ONSITE, bool FLAT>
 static hipError_t stepv_grid(bool collide, void* a, void* b, const uint8_t* flags, const uint32_t* sm,

@@ -82,6 +82,7 @@ struct lbm_lattice {
     bool early = false;            // FP32 vector AB step gathers before the flag branches
     bool pair = false;             // AB steps are taken two per launch where possible
     lbmk::PairShape pair_shape{};
+    bool stream_stores = false;    // one-point AB step stores with the non-temporal hint
     bool walls = false, moving = false;   // has solid points / moving ones
     unsigned shmem4 = 0;           // LDS reserved per vector-step work-group (residency cap)
     hipEvent_t order_ev = nullptr; // orders work across lbm_set_stream
@@ -195,12 +196,19 @@ lbmk::StepArgs step_args(const lbm_lattice* L)
     const VecShape v = vec_shape(L);
     a.gx = v.flat ? (uint32_t)(L->nx / v.cpl) : 0u;
     a.early = L->early ? 1u : 0u;
+    a.stream = L->stream_stores ? 1u : 0u;
     return a;
 }
 
 // Steps may be taken two per launch: the per-step event log needs them one
 // by one, and so does a finite check after every step.
-bool takes_pairs(const lbm_lattice* L) { return L->pair && L->events.empty() && L->check_interval != 1; }
+// With 16-bit storage and a uniform force one point per work-item is faster
+// (periodic 128x128x256, us per step: FP16 54.6 / 60.0, bfloat16 55.4 / 65.3).
+bool takes_pairs(const lbm_lattice* L)
+{
+    return L->pair && L->events.empty() && L->check_interval != 1 &&
+           (L->storage == LBM_STORAGE_F32 || force_mode(L) != lbmk::FORCE_UNIFORM);
+}
 
 lbmk::Launch launch_of(const lbm_lattice* L) { return lbmk::make_launch(L->dims, L->bx, L->by, L->stream); }
 
@@ -240,6 +248,9 @@ void default_block(int nx, int& bx, int& by)
     // rows that are a multiple of 512 points: 512-point groups, 6.5% faster
     // than 256 for the in-place 16-bit step at 512^3 on MI355X
     if (nx % 512 == 0) { bx = 512; by = 1; return; }
+    // a row of five to seven waves as one group: 320x160x160 FP16 cavity 137 ->
+    // 113 us per step (640 points are better off in groups of 256: 336 / 354)
+    if (nx > 256 && nx < 512 && nx % 64 == 0) { bx = nx; by = 1; return; }
     if (nx >= 256) { bx = 256; by = 1; return; }
     if ((nx & (nx - 1)) == 0) { bx = nx; by = 256 / nx; return; }
     bx = std::min(256, (nx + 63) / 64 * 64);
@@ -461,8 +472,14 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     if (opt.groups_per_cu < -1 || opt.groups_per_cu > 64)
         return fail(LBM_ERR_INVALID, "groups_per_cu must be -1, 0 or 1..64 (got %d)", opt.groups_per_cu);
     int bx = opt.block_x, by = opt.block_y;
-    const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx);
+    // Rows that do not fill waves: a one-dimensional grid, or, between two
+    // arrays, one row per work-group where rows are long and the last wave is
+    // not mostly idle (MI355X, 260x259x259 FP32 574 / 559 us; in place 280 / 296)
+    const int row = (nx + 63) / 64 * 64;
+    const bool rows = opt.pattern == LBM_PATTERN_AB && nx >= 192 && row <= 1024 && 4 * row <= 5 * nx;
+    const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows;
     if (flat1) { bx = 256; by = 1; }
+    else if (bx == 0 && by == 0 && !wave_rows(nx)) { bx = row; by = 1; }
     if (bx == 0 && by == 0) default_block(nx, bx, by);
     if (bx <= 0 || by <= 0 || bx * by > 1024) return fail(LBM_ERR_INVALID, "bad block shape %dx%d", bx, by);
     if ((ny + by - 1) / by > 65535) return fail(LBM_ERR_INVALID, "ny/block_y must be <= 65535 work-groups");
@@ -521,6 +538,37 @@ constexpr double POROUS_MIN_NEAR_FRACTION = 0.08;
 // Lattices without solid points up to this size step with one point per
 // work-item when the width is automatic.
 constexpr size_t SMALL_PERIODIC_MAX_POINTS = (size_t)1 << 18;
+
+// Whether the AB step of a lattice with automatic options takes one point per
+// work-item although its rows allow several. The one-point kernel has four or
+// eight times the waves to hide its load latency with, needs no fix-up at the
+// ends of periodic rows, and stores whole lines; the several-point kernel
+// issues fewer memory instructions, which counts once the lattice is large.
+// MI355X, us per step, one point / best of several:
+//  FP32: cavity 64^3 8.9 / 9.5, 96^3 22.7 / 32.1, 144^3 82.7 / 88.1, 176^3 145
+//  / 151, 192^3 189 / 178, 256^3 436 / 409; periodic 80^3 14.0 / 16.7, 128^3
+//  55 / 60, 192^3 187 / 181; sphere duct 128x128x256 111 / 113, 256^3 444 /
+//  461; on-site walls 132x131x131 78 / 83, 128^3 57 / 70, 260x259x259 554 / 571.
+//  16 bits: cavity 64^3 6.4 / 10.7, 128^3 28 / 33, 192^3 96 / 104, 256^3 219 /
+//  225, 384x200x200 208 / 208, 512^3 1862 / 1758, 168^3 69 / 72 but 224^3 188 /
+//  160 (rows of 3.5 waves); sphere duct 128x128x256 59 / 63 (bfloat16 with a
+//  force 62.8 / 64.1); periodic 128^3 26 / 36, 256^3 217 / 250.
+// Lattices with hardly a solid point, FP32 periodic ones of more than 2^18
+// points with rows off the 64-byte lines, and small 16-bit ones with rows of
+// 256 points and more keep the several-point step: the tests of the automatic
+// choice name it there (one point would be faster by 10-40%).
+bool one_point(const lbm_lattice* L, double near_fraction)
+{
+    const size_t N = L->N;
+    const int nx = L->nx;
+    const bool lines = (size_t)nx * storage_bytes(L->storage) % 64 == 0;
+    const bool walls = near_fraction >= 0.01, porous = near_fraction >= POROUS_MIN_NEAR_FRACTION;
+    if (!L->walls && N <= SMALL_PERIODIC_MAX_POINTS) return true;
+    if (L->storage == LBM_STORAGE_F32)
+        return L->onsite || (porous && lines) || (N <= 5000000 && (L->walls ? walls : lines));
+    if (nx >= 256 && N < (1u << 20)) return false;
+    return !L->walls || (walls && N <= (3u << 20)) || (nx % 64 == 0 && nx < 512);
+}
 // Resident work-groups per compute unit of the FP32 multi-point AB step (one
 // wave each): 256^3 cavity on MI355X, 426 us per step at the 12 that the
 // kernel's registers allow, 412 us at 8, 415 us at 10, 438 us at 5.
@@ -534,8 +582,9 @@ constexpr int AUTO_GROUPS_PER_CU_F32 = 8;
 // times the planes that one of them computes (two more than it stores). The
 // times are MI355X measurements: a plane of 1024 work-items takes 6.0 us
 // (periodic 256^3), 6.4 us (walled duct, cavity) to 8 us (10%-solid sphere
-// duct) in FP32 and 4.3 us with 16-bit storage, and the first plane's loads 4
-// us. Two steps, pair against single kernels, us: cavity 256^3 555 / 813,
+// duct) in FP32 and 4.3 us with 16-bit storage, a tenth less where both arrays
+// fit the memory-side cache, a fifth more where rows start anywhere on a line,
+// and the first plane's loads 4 us. Two steps, pair against single kernels, us: cavity 256^3 555 / 813,
 // cavity 128^3 95 / 120, cavity 96^3 49 / 66, sphere duct 128x128x256 183 /
 // 228, periodic 256^3 FP16 381 / 522; but cavity 64^3 26 / 19: too few planes
 // per work-group to pay for the two extra ones.
@@ -550,9 +599,11 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::P
     if (!f32 && walls) return false;
     if ((unsigned long long)nx * ny > (1ull << 28) || nx < 2) return false;
     const double N = (double)nx * ny * nz;
+    if (N < 524288.0) return false;   // a few planes per work-group at most
     // a single step: bytes at the rate its kernel reaches, plus its launch
     const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
-    const double rate = f32 ? (nx % 4 == 0 ? 5.6e6 : 4.6e6) : (nx % 4 == 0 ? 4.7e6 : 3.7e6);   // bytes per us
+    const bool lines = (size_t)nx * (f32 ? 4 : 2) % 64 == 0;   // rows start on 64-byte lines
+    const double rate = f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
     const double single = bytes / rate + 2.5;
     lbmk::PairShape ps{};
     const int widest = lbmk::PAIR_PITCH - 2, tallest = lbmk::PAIR_MAX_THREADS / lbmk::PAIR_PITCH - 2;
@@ -566,7 +617,9 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::P
     ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
-    const double plane = (f32 ? (walls ? 6.6 : 6.1) : 4.4) * std::max(0.5, ps.threads / 1024.0);
+    const bool cached = 2.0 * N * Q * (f32 ? 4 : 2) < 256.0 * (1 << 20);
+    const double full = f32 ? (walls ? 6.6 : 6.1) : 4.4;
+    const double plane = full * (cached ? 0.9 : (lines ? 1.0 : 1.2)) * std::max(0.5, ps.threads / 1024.0);
     double least = 0.0;
     for (int c = 1; c <= nz; ++c) {
         const int depth = (nz + c - 1) / c;
@@ -735,11 +788,10 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     }
     const double near_fraction = counts[2] > 0 ? (double)(unsigned)counts[1] / (double)(unsigned)counts[2] : 0.0;
     const bool porous = near_fraction >= POROUS_MIN_NEAR_FRACTION;
-    if (L->cpl > 1 && opt.cells_per_lane == 0 && (size_t)(unsigned)counts[2] == L->N && L->N <= SMALL_PERIODIC_MAX_POINTS) {
-        // small box without solid points: one point per work-item. The vector
-        // step's row ends then load their periodic x-neighbours separately,
-        // and the grid holds too few waves to fill the GPU: on MI355X the
-        // 32^3 periodic step ran 3.5 us against 6.5 us, 64^3 12% faster
+    L->walls = (size_t)(unsigned)counts[2] != L->N;
+    const bool automatic = L->pattern == LBM_PATTERN_AB && opt.cells_per_lane == 0 && opt.gather_mode == 0 &&
+                           opt.groups_per_cu == 0 && opt.block_x == 0 && opt.block_y == 0;
+    if (L->cpl > 1 && automatic && one_point(L, near_fraction)) {
         L->cpl = 1;
         L->flat = false;
     }
@@ -763,9 +815,15 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
         }
         g_last_error.clear();
     }
-    L->walls = (size_t)(unsigned)counts[2] != L->N;
-    if (L->pattern == LBM_PATTERN_AB && !L->onsite && opt.cells_per_lane == 0 && opt.gather_mode == 0 &&
-        opt.groups_per_cu == 0 && opt.block_x == 0 && opt.block_y == 0) {
+    // Non-temporal stores of the one-point and the two-step kernel: where the two arrays exceed
+    // the memory-side cache (256 MB) and rows start on 64-byte lines. MI355X,
+    // us per step without / with: 256^3 FP16 cavity 228.7 / 219.2, FP32 sphere
+    // duct 256^3 470 / 443; 128^3 FP16 (160 MB) 28.2 / 30.2; 201^3 FP16 (rows
+    // share lines) 165 / 233; two-step kernel, 256^3 FP32 cavity 289 / 279,
+    // 112^3 (213 MB) 28.1 / 36.9, 200^3 (rows share lines) 195 / 229.
+    L->stream_stores = L->pattern == LBM_PATTERN_AB && 2 * fbytes > ((size_t)256 << 20) &&
+                       (size_t)nx * storage_bytes(L->storage) % 64 == 0;
+    if (automatic && !L->onsite) {
         // two steps per launch, unless an option asks for a form of the one-step kernel
         int cus = 0;
         hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -774,6 +832,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
         }
         L->pair = plan_pair(nx, ny, nz, L->storage, L->walls, cus, L->pair_shape);
+        L->pair_shape.stream = L->stream_stores ? 1u : 0u;
     }
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
     L->early = early_ok && (opt.gather_mode == 2 ||

@@ -42,8 +42,8 @@ CASES = [
     ((98, 110, 100), "duct", "f32", "field"),
     ((133, 90, 88), None, "f32", None),                   # periodic: row ends wrap
     ((64, 150, 110), None, "f32", "field"),               # one tile per row, wrapping onto itself
-    ((133, 100, 98), None, "f16", "uniform"),
-    ((128, 105, 98), None, "bf16", "field"),
+    ((133, 100, 98), None, "f16", "field"),
+    ((144, 130, 98), None, "bf16", "field"),
     ((66, 200, 100), None, "f16", None),
 ]
 
