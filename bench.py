@@ -63,7 +63,8 @@ def kernel_source_hash():
     with the counter summaries so that the benchmark reports traffic only for
     the kernels the counters were taken on."""
     h = hashlib.sha256()
-    for name in ("d3q19.hpp", "kernels_step.hip", "kernels_pair.hip", "kernels.hpp"):
+    for name in ("d3q19.hpp", "step_common.hpp", "kernels_step.hip", "kernels_point.hip", "kernels_pair.hip",
+                 "kernels.hpp"):
         with open(os.path.join(ROOT, "paper_1309_1983_amd", "csrc", name), encoding="utf-8") as fh:
             h.update(_code_of(fh.read()).encode())
     return h.hexdigest()[:16]
@@ -140,9 +141,9 @@ def _algorithmic_bytes_per_point(kernel):
     loads and 19 stores of the storage width for a step or for the two steps
     of the two-step kernel, plus the force field when the step reads one;
     264 B for the reverse step; None otherwise."""
-    if kernel.startswith("lbmk::k_adj_stepv"):
+    if kernel.startswith("lbmk::k_adj_step"):
         return ADJOINT_REVERSE_BYTES
-    for pre in ("lbmk::k_step_pair<", "lbmk::k_step_abv<", "lbmk::k_step_aa0<", "lbmk::k_step_aa1<"):
+    for pre in ("lbmk::k_step_pair<", "lbmk::k_step_abv<", "lbmk::k_step_ab<", "lbmk::k_step_aa0<", "lbmk::k_step_aa1<"):
         if kernel.startswith(pre):
             args = [a.strip() for a in kernel[len(pre):-1].split(",")]
             width = 4 if args[0].endswith("StF32") else 2

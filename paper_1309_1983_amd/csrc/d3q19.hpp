@@ -169,8 +169,14 @@ __device__ __forceinline__ void stv_nt(B* base, uint32_t idx, typename Vec<B, VW
     }
 }
 
-// The same for one element, as a global store (16-bit raw buffer stores were
-// 4% slower on the sphere duct).
+template <class T>
+__device__ __forceinline__ T ld_nt(const T* base, uint32_t idx)
+{
+    return __builtin_nontemporal_load(reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + idx * (uint32_t)sizeof(T)));
+}
+
+// Streaming store of one element, as a global store (16-bit raw buffer stores
+// were 4% slower on the sphere duct).
 template <class T>
 __device__ __forceinline__ void st_nt(T* base, uint32_t idx, T v)
 {

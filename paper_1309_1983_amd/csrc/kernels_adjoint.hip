@@ -140,33 +140,48 @@ __device__ __forceinline__ void adj_cell(const float av[Q], const float h[Q], fl
     tterm = fmaf(0.5f, tg, tt) * inv_tau2;
 }
 
-// Block sum of per-work-item tau terms in double with a fixed-shape LDS tree
-// (any block size, deterministic); thread 0 adds it to this block's slot.
+// Sum of the work-items' tau terms in double, in an order fixed by the group's
+// shape: within each wave by lane exchange, then over the waves by one
+// work-item, which adds it to this work-group's slot. Every work-item of the
+// group takes part.
 __device__ __forceinline__ void block_tau_sum(double v, double* __restrict__ taupart)
 {
-    __shared__ double part[1024];
+    __shared__ double part[16];
     const int tid = threadIdx.y * blockDim.x + threadIdx.x;
-    const int nthreads = blockDim.x * blockDim.y;
-    part[tid] = v;
-    __syncthreads();
-    int span = 1;
-    while (span < nthreads) span <<= 1;
-    for (int sh = span >> 1; sh > 0; sh >>= 1) {
-        if (tid < sh && tid + sh < nthreads) part[tid] += part[tid + sh];
+    const int nwaves = (int)(blockDim.x * blockDim.y + 63) / 64;
+    const int lanes = min(64, (int)(blockDim.x * blockDim.y) - (tid & ~63));   // of this wave
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) {
+        const double w = __shfl_down(v, sh);
+        if ((tid & 63) + sh < lanes) v += w;
+    }
+    if (nwaves > 1) {
+        if ((tid & 63) == 0) part[tid >> 6] = v;
         __syncthreads();
     }
     if (tid == 0) {
+        for (int k = 1; k < nwaves; ++k) v += part[k];
         const size_t blk = (size_t)blockIdx.x + (size_t)gridDim.x * ((size_t)blockIdx.y + (size_t)gridDim.y * blockIdx.z);
-        taupart[blk] += part[0];
+        taupart[blk] += v;
     }
 }
 
-template <int FM, bool DIRECT>
+// Reverse step, one point per work-item: bound by its 264 bytes per point
+// (256^3 duct 805 us = 5.5 TB/s; two points per work-item, whose 168 registers
+// leave three waves per SIMD, 862 us = 5.1 TB/s). Wall links come from the bit
+// masks instead of up to 36 neighbour flags. Every work-item of a wave with a
+// fluid point stores, zeros at solid points: skipping them left holes in the
+// lines, which memory then reads before it writes (packed spheres at 256^3
+// 1056 -> 842 us). STREAM, for states that the caches do not hold: b, dL/dF and
+// the rows of s that one wave alone reads pass by them (256^3 duct 809 -> 795).
+template <int FM, bool DIRECT, bool STREAM>
 __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
                                                    const float* __restrict__ bin,
                                                    float* __restrict__ bout, float* __restrict__ gF,
                                                    double* __restrict__ taupart,
                                                    const uint8_t* __restrict__ flags,
+                                                   const uint32_t* __restrict__ smask,
+                                                   const uint32_t* __restrict__ mmask,
                                                    const float* __restrict__ ff, StepArgs a,
                                                    float inv_tau2)
 {
@@ -178,10 +193,15 @@ __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
     const uint32_t o = inside ? (uint32_t)y * (uint32_t)d.nx + (uint32_t)x : 0u;
     const uint32_t c = z * d.nxy + o;
     const uint8_t fl = inside ? flags[c] : (uint8_t)1;
+    const bool fluid = (fl & TYPE_MASK) == 0;
     float tterm = 0.0f;
+    float b[Q], g[3];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) b[i] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) g[k] = 0.0f;
 
-    if (!(fl & TYPE_MASK)) {
-        const size_t N = d.N;
+    if (fluid) {
         const uint32_t zm = wrap_m(z, (uint32_t)d.nz), zp = wrap_p(z, (uint32_t)d.nz);
         uint32_t on[Q];
         pull_offsets(d, x, y, on);
@@ -189,39 +209,49 @@ __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             // a_i(x) arrives from b_i(x + e_i); x + e_i is the pull source of opp(i)
-            av[i] = DIRECT ? ld(plane(bin, d, i, z), o)
-                           : ld(plane(bin, d, i, src_slab(OPP[i], z, zm, zp)), on[OPP[i]]);
-            h[i] = ld(plane(s, d, i, src_slab(i, z, zm, zp)), on[i]);
+            const float* pa = DIRECT ? plane(bin, d, i, z) : plane(bin, d, i, src_slab(OPP[i], z, zm, zp));
+            const uint32_t oa = DIRECT ? o : on[OPP[i]];
+            const float* ps = plane(s, d, i, src_slab(i, z, zm, zp));
+            av[i] = ld(pa, oa);
+            // without an x-shift no other wave reads the line
+            h[i] = STREAM && EX[i] == 0 ? ld_nt(ps, on[i]) : ld(ps, on[i]);
         }
         uint32_t mwmask = 0;
         if (fl & NEAR_WALL) {
+            const uint32_t solid = smask[c];   // bit i: x - e_i is solid
+            if (fl & NEAR_MOVING) mwmask = mmask[c];
 #pragma unroll
-            for (int i = 1; i < Q; ++i) {
-                const uint8_t nf = flags[src_slab(i, z, zm, zp) * d.nxy + on[i]];
-                if (nf & TYPE_MASK) {
+            for (int i = 1; i < Q; ++i)
+                if ((solid >> i) & 1u) {
                     h[i] = ld(plane(s, d, OPP[i], z), o);
-                    if (nf & MOVING) mwmask |= 1u << i;
+                    // x + e_opp(i) = x - e_i: that adjoint arrives by the bounced link
+                    if (!DIRECT) av[OPP[i]] = ld(plane(bin, d, i, z), o);
                 }
-                // x + e_i solid: the adjoint arrives by the bounced link
-                const int k = OPP[i];
-                if (!DIRECT && (flags[src_slab(k, z, zm, zp) * d.nxy + on[k]] & TYPE_MASK))
-                    av[i] = ld(plane(bin, d, k, z), o);
-            }
         }
+        float Fx, Fy, Fz;
+        force_at<FM>(a, ff, c, Fx, Fy, Fz);
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             h[i] = h[i] - weight(i);
             if (i > 0 && ((mwmask >> i) & 1u)) h[i] = h[i] + a.mw[i];
         }
-        float Fx, Fy, Fz;
-        force_at<FM>(a, ff, c, Fx, Fy, Fz);
-        float b[Q], gx, gy, gz;
-        adj_cell<FORCE>(av, h, Fx, Fy, Fz, a, inv_tau2, b, gx, gy, gz, tterm);
+        adj_cell<FORCE>(av, h, Fx, Fy, Fz, a, inv_tau2, b, g[0], g[1], g[2], tterm);
+    }
+    // solid points take part with zeros: lines with holes would be written back in part
+    if (inside && __builtin_amdgcn_ballot_w64(fluid) != 0ull) {
+        float old[3];
 #pragma unroll
-        for (int j = 0; j < Q; ++j) st(plane(bout, d, j, z), o, b[j]);
-        gF[c] += gx;
-        gF[N + c] += gy;
-        gF[2 * N + c] += gz;
+        for (int k = 0; k < 3; ++k) old[k] = ld(gF + k * (size_t)d.N, c);
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            if (STREAM) st_nt(plane(bout, d, j, z), o, b[j]);
+            else st(plane(bout, d, j, z), o, b[j]);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            if (STREAM) st_nt(gF + k * (size_t)d.N, c, old[k] + g[k]);
+            else st(gF + k * (size_t)d.N, c, old[k] + g[k]);
+        }
     }
 
     block_tau_sum((double)tterm, taupart);
@@ -402,15 +432,15 @@ hipError_t launch_adjoint_seed(int fm, const float* f, const uint8_t* flags, con
     return hipGetLastError();
 }
 
-template <int FM>
+template <int FM, bool STREAM>
 static hipError_t adj_fm(bool direct, const float* s, const float* bin, float* bout, float* gF,
-                         double* tp, const uint8_t* flags, const float* ff, const StepArgs& a,
-                         float it2, const Launch& L)
+                         double* tp, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm, const float* ff,
+                         const StepArgs& a, float it2, const Launch& L)
 {
     if (direct)
-        hipLaunchKernelGGL((k_adj_step<FM, true>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_step<FM, true, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
     else
-        hipLaunchKernelGGL((k_adj_step<FM, false>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_step<FM, false, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
     return hipGetLastError();
 }
 
@@ -447,15 +477,24 @@ hipError_t launch_adjoint_stepv(int vw, bool direct, int fm, const float* s, con
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_adjoint_step(bool direct, int fm, const float* s, const float* bin, float* bout,
-                               float* gF, double* taupart, const uint8_t* flags, const float* ff,
-                               const StepArgs& args, float inv_tau2, const Launch& L)
+template <bool STREAM>
+static hipError_t adj_stream(bool direct, int fm, const float* s, const float* bin, float* bout,
+                             float* gF, double* taupart, const uint8_t* flags, const uint32_t* smask,
+                             const uint32_t* mmask, const float* ff, const StepArgs& args, float inv_tau2, const Launch& L)
 {
     switch (fm) {
-    case FORCE_UNIFORM: return adj_fm<FORCE_UNIFORM>(direct, s, bin, bout, gF, taupart, flags, ff, args, inv_tau2, L);
-    case FORCE_FIELD: return adj_fm<FORCE_FIELD>(direct, s, bin, bout, gF, taupart, flags, ff, args, inv_tau2, L);
-    default: return adj_fm<FORCE_NONE>(direct, s, bin, bout, gF, taupart, flags, ff, args, inv_tau2, L);
+    case FORCE_UNIFORM: return adj_fm<FORCE_UNIFORM, STREAM>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
+    case FORCE_FIELD: return adj_fm<FORCE_FIELD, STREAM>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
+    default: return adj_fm<FORCE_NONE, STREAM>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
     }
+}
+
+hipError_t launch_adjoint_step(bool direct, int fm, const float* s, const float* bin, float* bout,
+                               float* gF, double* taupart, const uint8_t* flags, const uint32_t* smask,
+                               const uint32_t* mmask, const float* ff, const StepArgs& args, float inv_tau2, const Launch& L)
+{
+    return args.stream ? adj_stream<true>(direct, fm, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L)
+                       : adj_stream<false>(direct, fm, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
 }
 
 }  // namespace lbmk

@@ -269,12 +269,19 @@ void adjoint_block(int nx, int& bx, int& by)
     }
 }
 
-// Launch of the reverse step: two x-points per work-item with 64-work-item
-// groups (the fastest shape measured at 256^3; four points need too many
-// registers), else one point per work-item with at most 256 per group.
+// Launch of the reverse step: one point per work-item with at most 256 per
+// group, its rows one after the other where they do not fill waves. Against
+// two points per work-item (us per reverse step, two / one): 32^3 duct 13.9 /
+// 10.6, 64^3 22.7 / 21.0, 100^3 65.4 / 60.5, 128^3 116 / 110, 100x512x128 355 /
+// 348, 256^3 duct 862 / 805, packed spheres 1056 / 842. The exception: planes
+// that do not begin on 64-byte lines, in lattices that the caches do not hold.
+// There every wave's stores share lines with two other waves', and two points
+// per work-item halve the number of shared lines: 118x110x110 91 / 92,
+// 130x258x258 478 / 494, 132x131x131 137 / 151 (but 100x90x90 59 / 52).
+// The choice depends on the sizes alone, so that the workspace size does too.
 lbmk::Launch adjoint_launch(const d3q19::Dims& dims, bool vec_ok, hipStream_t stream, bool& vec)
 {
-    vec = vec_ok && dims.nx % 2 == 0;
+    vec = vec_ok && dims.nx % 2 == 0 && dims.nxy % 16 != 0 && dims.N >= (1u << 20);
     if (vec) {
         d3q19::Dims q = dims;
         q.nx = dims.nx / 2;
@@ -1396,7 +1403,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
                                                      LR));
             else
                 HIPCHK(L, lbmk::launch_adjoint_step(direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part, L->d_flags,
-                                                    L->d_force, rargs, inv_tau2, LR));
+                                                    L->d_smask, L->d_mmask, L->d_force, rargs, inv_tau2, LR));
             ab ^= 1;
             direct = false;
         }
