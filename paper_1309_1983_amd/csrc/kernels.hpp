@@ -67,11 +67,12 @@ struct PairShape {
     uint32_t stream;             // store with the non-temporal hint
 };
 // `a` holds the state, `b` receives the state two steps later. walls: the
-// lattice has solid points (FP32 storage only); moving: some of them move.
+// lattice has solid points (FP32 storage only); moving: some of them move;
+// onsite: it has on-site velocity nodes (FP32 without force or moving points).
 // name non-null: reports the kernel instead of launching it.
 hipError_t launch_step_pair(int storage, int force_mode, const void* a, void* b, const uint8_t* flags,
                             const uint32_t* smask, const uint32_t* mmask, const float* ffield, const StepArgs& args,
-                            const PairShape& ps, bool walls, bool moving, hipStream_t s,
+                            const PairShape& ps, bool walls, bool moving, bool onsite, hipStream_t s,
                             const void** name = nullptr);
 
 // The kernel (host-side function pointer) that launch_step_abv (vector) or

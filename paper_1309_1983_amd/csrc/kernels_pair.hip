@@ -76,7 +76,7 @@ __device__ __forceinline__ void store_or_drop(B v, B* base, uint32_t bytes, uint
 // The march of one (x, y) column along the planes z0 .. z0 + depth - 1.
 // OUT: the wave holds output points; the others only provide s^{t+1} of the
 // halo, and take the same barriers.
-template <class St, int FM, bool WALLS, bool MOVING, bool STREAM, bool OUT>
+template <class St, int FM, bool WALLS, bool MOVING, bool ONSITE, bool STREAM, bool OUT>
 __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict__ src,
                                            typename St::bits_t* __restrict__ dst, const uint8_t* __restrict__ flags,
                                            const uint32_t* __restrict__ smask, const uint32_t* __restrict__ mmask,
@@ -169,6 +169,16 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
         bgk_collide<FORCE>(h, a.omega, a.cF, Fx, Fy, Fz);
     };
 
+    // Rebuilds the unknowns of on-site nodes from their neighbour bits, as the
+    // one-step kernels do before they collide.
+    static_assert(!(ONSITE && FORCE), "the forced kernels have no registers left for the rebuild");
+    auto rebuild = [&](uint32_t m) {
+        if (!ONSITE || !((m >> 24) & ONSITE_NODE)) return;
+        const bool mv = ((m >> 24) & ONSITE_MOVING) != 0u;
+        onsite_rebuild<false>(h, m & BITS, mv ? a.uw[0] : 0.0f, mv ? a.uw[1] : 0.0f, mv ? a.uw[2] : 0.0f, 0.0f, 0.0f,
+                              0.0f);
+    };
+
     force_at(z0 - 1, F0);
     fetch(wrapz(z0 - 1), m0, w0);
     decode();
@@ -185,6 +195,7 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
 
     for (int it = 0; it < depth + 2; ++it) {
         const int zt = z0 - 1 + it;   // plane of s^{t+1}
+        rebuild(m0);   // before the loads, whose registers it can use
         uint32_t sm2 = 0, v2 = 0, fl3 = 0;
         // the wave issues its loads at raised priority: they get into the
         // memory pipeline before other waves' arithmetic (3% on the cavity)
@@ -229,6 +240,7 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
             }
 #pragma unroll
             for (int i = 0; i < Q; ++i) h[i] = St::off_b(q[i], i);
+            rebuild(mp);
             point(wp, vp, Fp);
             if (WALLS) {
                 // solid points inside a tile are stored as the rest state, as
@@ -276,7 +288,7 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
 
 }  // namespace
 
-template <class St, int FM, bool WALLS, bool MOVING, bool STREAM>
+template <class St, int FM, bool WALLS, bool MOVING, bool ONSITE, bool STREAM>
 __global__ __launch_bounds__(NT, NT / 256) void k_step_pair(const typename St::bits_t* __restrict__ src,
                                                             typename St::bits_t* __restrict__ dst,
                                                             const uint8_t* __restrict__ flags,
@@ -316,59 +328,63 @@ __global__ __launch_bounds__(NT, NT / 256) void k_step_pair(const typename St::b
     x = x < 0 ? x + d.nx : (x >= d.nx ? x - d.nx : x);
     y = y < 0 ? y + d.ny : (y >= d.ny ? y - d.ny : y);
     if (!WALLS || __builtin_amdgcn_ballot_w64(out) != 0ull)
-        pair_march<St, FM, WALLS, MOVING, STREAM, true>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
+        pair_march<St, FM, WALLS, MOVING, ONSITE, STREAM, true>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
     else
-        pair_march<St, FM, WALLS, MOVING, STREAM, false>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
+        pair_march<St, FM, WALLS, MOVING, ONSITE, STREAM, false>(src, dst, flags, smask, mmask, ff, a, ex, x, y, z0, depth, lidx, out);
 }
 
-template <class St, int FM, bool WALLS, bool MOVING, bool STREAM>
+template <class St, int FM, bool WALLS, bool MOVING, bool ONSITE, bool STREAM>
 static hipError_t pair_stream(const void* a, void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
                               const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
 {
     using B = typename St::bits_t;
     if (name) {
-        *name = reinterpret_cast<const void*>(&k_step_pair<St, FM, WALLS, MOVING, STREAM>);
+        *name = reinterpret_cast<const void*>(&k_step_pair<St, FM, WALLS, MOVING, ONSITE, STREAM>);
         return hipSuccess;
     }
-    hipLaunchKernelGGL((k_step_pair<St, FM, WALLS, MOVING, STREAM>), dim3((ps.groups + 7u) / 8u * 8u), dim3(ps.threads), 0,
+    hipLaunchKernelGGL((k_step_pair<St, FM, WALLS, MOVING, ONSITE, STREAM>), dim3((ps.groups + 7u) / 8u * 8u), dim3(ps.threads), 0,
                        s, static_cast<const B*>(a), static_cast<B*>(b), flags, sm, mm, ff, args, ps);
     return hipGetLastError();
 }
 
-template <class St, int FM, bool WALLS, bool MOVING>
+template <class St, int FM, bool WALLS, bool MOVING, bool ONSITE>
 static hipError_t pair_launch(const void* a, void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
                               const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
 {
-    return ps.stream ? pair_stream<St, FM, WALLS, MOVING, true>(a, b, flags, sm, mm, ff, args, ps, s, name)
-                     : pair_stream<St, FM, WALLS, MOVING, false>(a, b, flags, sm, mm, ff, args, ps, s, name);
+    return ps.stream ? pair_stream<St, FM, WALLS, MOVING, ONSITE, true>(a, b, flags, sm, mm, ff, args, ps, s, name)
+                     : pair_stream<St, FM, WALLS, MOVING, ONSITE, false>(a, b, flags, sm, mm, ff, args, ps, s, name);
 }
 
-template <class St, bool WALLS, bool MOVING>
+template <class St, bool WALLS, bool MOVING, bool ONSITE>
 static hipError_t pair_fm(int fm, const void* a, void* b, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
                           const float* ff, const StepArgs& args, const PairShape& ps, hipStream_t s, const void** name)
 {
     switch (fm) {
     case FORCE_UNIFORM:   // FP32 only
         if constexpr (sizeof(typename St::bits_t) == 4)
-            return pair_launch<St, FORCE_UNIFORM, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
+            return pair_launch<St, FORCE_UNIFORM, WALLS, MOVING, ONSITE>(a, b, flags, sm, mm, ff, args, ps, s, name);
         return hipErrorInvalidValue;
-    case FORCE_FIELD: return pair_launch<St, FORCE_FIELD, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
-    default: return pair_launch<St, FORCE_NONE, WALLS, MOVING>(a, b, flags, sm, mm, ff, args, ps, s, name);
+    case FORCE_FIELD: return pair_launch<St, FORCE_FIELD, WALLS, MOVING, ONSITE>(a, b, flags, sm, mm, ff, args, ps, s, name);
+    default: return pair_launch<St, FORCE_NONE, WALLS, MOVING, ONSITE>(a, b, flags, sm, mm, ff, args, ps, s, name);
     }
 }
 
 hipError_t launch_step_pair(int storage, int fm, const void* a, void* b, const uint8_t* flags, const uint32_t* sm,
                             const uint32_t* mm, const float* ff, const StepArgs& args, const PairShape& ps, bool walls,
-                            bool moving, hipStream_t s, const void** name)
+                            bool moving, bool onsite, hipStream_t s, const void** name)
 {
     if (ps.rows < 3 || ps.rows * P > (uint32_t)NT || ps.tx + 2 > (uint32_t)P || ps.threads > (uint32_t)NT ||
         ps.rows * (ps.tx + 2) > ps.threads)
         return hipErrorInvalidValue;
-    if (storage == 0 && walls && moving) return pair_fm<StF32, true, true>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
-    if (storage == 0 && walls) return pair_fm<StF32, true, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
-    if (storage == 0) return pair_fm<StF32, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
-    if (storage == 1 && !walls) return pair_fm<StF16, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
-    if (storage == 2 && !walls) return pair_fm<StBF16, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
+    if (onsite) {
+        if (storage != 0 || !walls || moving || fm != FORCE_NONE) return hipErrorInvalidValue;
+        return pair_launch<StF32, FORCE_NONE, true, false, true>(a, b, flags, sm, mm, ff, args, ps, s, name);
+    }
+    if (storage == 0 && walls && moving) return pair_fm<StF32, true, true, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
+    if (storage == 0 && walls) return pair_fm<StF32, true, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
+    if (storage == 0) return pair_fm<StF32, false, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
+    if (storage == 1 && !walls) return pair_fm<StF16, false, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
+    if (storage == 2 && !walls) return pair_fm<StBF16, false, false, false>(fm, a, b, flags, sm, mm, ff, args, ps, s, name);
     return hipErrorInvalidValue;
 }
 

@@ -207,7 +207,8 @@ lbmk::StepArgs step_args(const lbm_lattice* L)
 bool takes_pairs(const lbm_lattice* L)
 {
     return L->pair && L->events.empty() && L->check_interval != 1 &&
-           (L->storage == LBM_STORAGE_F32 || force_mode(L) != lbmk::FORCE_UNIFORM);
+           (L->storage == LBM_STORAGE_F32 || force_mode(L) != lbmk::FORCE_UNIFORM) &&
+           (!L->onsite || force_mode(L) == lbmk::FORCE_NONE);
 }
 
 lbmk::Launch launch_of(const lbm_lattice* L) { return lbmk::make_launch(L->dims, L->bx, L->by, L->stream); }
@@ -600,7 +601,14 @@ constexpr int AUTO_GROUPS_PER_CU_F32 = 8;
 // bound by its memory instructions and arithmetic rather than by HBM, and
 // with walls it only drew level (256^3 FP16 cavity 436 / 446 us) or lost
 // (sphere duct 150 / 134).
-bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::PairShape& best)
+//
+// On-site walls cost a plane 8.4 us and more (the rebuild runs in every wave
+// that holds a box side), and no less where the arrays fit the cache; their
+// single step reaches 5.8 TB/s, off the lines 5.1 or 4.7. us per step, single /
+// pair: 132x131x131 77.7 / 67.8, 256^3 432 / 361, 182x193x490 656 / 537; but
+// 128^3 56.2 / 58.2, 160^3 107 / 124, 140x110x150 76 / 86, 139x131x131 (363 MB) 89 / 97,
+// 130x128x107 (271 MB) 48 / 52, 112^3 (213 MB) 39 / 46.
+bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, int cus, lbmk::PairShape& best)
 {
     const bool f32 = storage == LBM_STORAGE_F32;
     if (!f32 && walls) return false;
@@ -610,7 +618,8 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::P
     // a single step: bytes at the rate its kernel reaches, plus its launch
     const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
     const bool lines = (size_t)nx * (f32 ? 4 : 2) % 64 == 0;   // rows start on 64-byte lines
-    const double rate = f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
+    const double rate = onsite ? (lines ? 5.8e6 : ((size_t)nx * ny % 16 == 0 ? 5.1e6 : 4.7e6))
+                               : f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
     const double single = bytes / rate + 2.5;
     lbmk::PairShape ps{};
     const int widest = lbmk::PAIR_PITCH - 2, tallest = lbmk::PAIR_MAX_THREADS / lbmk::PAIR_PITCH - 2;
@@ -625,8 +634,16 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, int cus, lbmk::P
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
     const bool cached = 2.0 * N * Q * (f32 ? 4 : 2) < 256.0 * (1 << 20);
-    const double full = f32 ? (walls ? 6.6 : 6.1) : 4.4;
+    if (onsite && bytes < (nx % 4 == 0 ? 320e6 : 400e6)) return false;   // largely held by the cache
+    const double full = onsite ? 8.4 : f32 ? (walls ? 6.6 : 6.1) : 4.4;
     const double plane = full * (cached ? 0.9 : (lines ? 1.0 : 1.2)) * std::max(0.5, ps.threads / 1024.0);
+    // a few columns short of whole 64-byte lines: take them (us per step, before
+    // / after: 140x110x150 cavity 47 columns 69.9 / 65.6, 292x192x401 59
+    // columns 616 / 574, 245x216x126 periodic 62 columns 148 / 134)
+    if (nx % 16 != 0 && ps.tx % 16u >= 11u) {
+        ps.tx = (ps.tx + 15u) / 16u * 16u;
+        ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
+    }
     double least = 0.0;
     for (int c = 1; c <= nz; ++c) {
         const int depth = (nz + c - 1) / c;
@@ -830,7 +847,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     // 112^3 (213 MB) 28.1 / 36.9, 200^3 (rows share lines) 195 / 229.
     L->stream_stores = L->pattern == LBM_PATTERN_AB && 2 * fbytes > ((size_t)256 << 20) &&
                        (size_t)nx * storage_bytes(L->storage) % 64 == 0;
-    if (automatic && !L->onsite) {
+    if (automatic && !(L->onsite && (L->moving || L->storage != LBM_STORAGE_F32))) {
         // two steps per launch, unless an option asks for a form of the one-step kernel
         int cus = 0;
         hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
@@ -838,7 +855,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             lbm_destroy(L);
             return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
         }
-        L->pair = plan_pair(nx, ny, nz, L->storage, L->walls, cus, L->pair_shape);
+        L->pair = plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, cus, L->pair_shape);
         L->pair_shape.stream = L->stream_stores ? 1u : 0u;
     }
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
@@ -970,7 +987,7 @@ lbm_status lbm_step_kernel_name(lbm_lattice* L, char* buf, size_t cap)
     const void* fn = nullptr;
     if (takes_pairs(L))
         HIPCHK(L, lbmk::launch_step_pair(L->storage, force_mode(L), nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                         step_args(L), L->pair_shape, L->walls, L->moving, L->stream, &fn));
+                                         step_args(L), L->pair_shape, L->walls, L->moving, L->onsite, L->stream, &fn));
     else
         HIPCHK(L, lbmk::resolve_step_kernel(vector, L->storage, L->pattern, L->parity, vec_shape(L).cpl, true, force_mode(L),
                                         L->d_f[L->cur], L->d_f[L->cur ^ 1], L->d_flags, L->d_smask, L->d_mmask,
@@ -1437,7 +1454,7 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
         if (pairs && n - s >= 2 && !(rho && n - s == 2) &&
             (L->check_interval == 0 || (L->steps_done + 1) % L->check_interval != 0)) {
             HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
-                                             L->d_force, args, L->pair_shape, L->walls, L->moving, L->stream));
+                                             L->d_force, args, L->pair_shape, L->walls, L->moving, L->onsite, L->stream));
             L->cur ^= 1;
             L->steps_done += 2;
             ++s;

@@ -31,7 +31,7 @@ def _flags(kind, shape):
         return W.random_flags(N, 5, 0.15, 0.05)
     if kind == "random_resting":
         return W.random_flags(N, 6, 0.1, 0.0)
-    return {"cavity": W.cavity_flags, "duct": W.duct_flags}[kind](*shape) if kind else None
+    return {"cavity": W.cavity_flags, "duct": W.duct_flags, "onsite": W.onsite_cavity_flags}[kind](*shape) if kind else None
 
 
 CASES = [
@@ -45,6 +45,10 @@ CASES = [
     ((133, 100, 98), None, "f16", "field"),
     ((144, 130, 98), None, "bf16", "field"),
     ((66, 200, 100), None, "f16", None),
+    ((132, 131, 131), "onsite", "f32", None),             # on-site nodes on faces, edges and corners
+    ((223, 120, 100), "onsite", "f32", None),
+    ((140, 110, 98), "cavity", "f32", None),              # 47 columns taken as 48
+    ((184, 130, 98), None, "f16", None),                  # 62 as 64
 ]
 
 
@@ -65,7 +69,7 @@ def _lattice(shape, flags, storage, force, **kw):
 def test_two_steps_per_launch_equal_single_steps(case):
     shape, kind, storage, force = CASES[case]
     flags = _flags(kind, shape)
-    fl = slice(None) if flags is None else torch.from_numpy(flags == 0).cuda()
+    fl = slice(None) if flags is None else torch.from_numpy((flags != 1) & (flags != 2)).cuda()
     one, two = (_lattice(shape, flags, storage, force) for _ in range(2))
     assert "k_step_pair" in two.step_kernel_name(), (shape, two.step_kernel_name())
     done = 0
@@ -101,6 +105,15 @@ def test_pairs_leave_output_steps_checks_and_options_as_they_are():
     lat.set_populations(f)
     with pytest.raises(LBMError, match="NONFINITE"):
         lat.step(2)
+    lat.close()
+    # on-site nodes under a force, or beside moving walls, keep single steps
+    flags = _flags("onsite", (223, 120, 100))
+    lat = _lattice((223, 120, 100), flags, "f32", "uniform")
+    assert "k_step_pair" not in lat.step_kernel_name()
+    lat.close()
+    flags[(flags == 1) & (np.arange(flags.size) < 223 * 120)] = 2
+    lat = _lattice((223, 120, 100), flags, "f32", None)
+    assert "k_step_pair" not in lat.step_kernel_name()
     lat.close()
     # the event log and the one-step kernel's options keep single steps
     for kw in ({"timing": 8}, {"cells_per_lane": 1}, {"block": (64, 1)}, {"gather_mode": "early", "cells_per_lane": 0},
