@@ -64,7 +64,7 @@ def kernel_source_hash():
     the kernels the counters were taken on."""
     h = hashlib.sha256()
     for name in ("d3q19.hpp", "step_common.hpp", "kernels_step.hip", "kernels_point.hip", "kernels_pair.hip",
-                 "kernels.hpp"):
+                 "kernels_box.hip", "kernels.hpp"):
         with open(os.path.join(ROOT, "paper_1309_1983_amd", "csrc", name), encoding="utf-8") as fh:
             h.update(_code_of(fh.read()).encode())
     return h.hexdigest()[:16]

@@ -217,9 +217,11 @@ lbm_status lbm_set_stream(lbm_lattice* lat, void* hip_stream);
 /* Name of the device kernel the next lbm_step launches (the fused step of
  * Algorithm 3 in the variant the lattice's storage, pattern, parity, force
  * and geometry select; on lattices whose steps are taken two per launch, the
- * two-step kernel, which lbm_step launches for n >= 2), as the HIP runtime
- * reports it, demangled; written to buf (NUL-terminated, truncated to cap bytes). For measurement tools that
- * match it against profiler traces. Errors: LBM_ERR_INVALID for a NULL or
+ * two-step kernel, which lbm_step launches for n >= 2; small lattices, whose
+ * pairs of steps run on boxes in local memory, report the kernel of a single
+ * step), as the HIP runtime reports it, demangled; written to buf
+ * (NUL-terminated, truncated to cap bytes). For measurement tools that match
+ * it against profiler traces. Errors: LBM_ERR_INVALID for a NULL or
  * empty buffer. */
 lbm_status lbm_step_kernel_name(lbm_lattice* lat, char* buf, size_t cap);
 
@@ -245,8 +247,8 @@ lbm_status lbm_set_force_field(lbm_lattice* lat, const float* F_dev);
  * u_dev [3][N] or NULL (u = 0). */
 lbm_status lbm_init_equilibrium(lbm_lattice* lat, const float* rho_dev, const float* u_dev);
 
-/* Enqueues n fused pull steps (Algorithm 3). n = 0 is a no-op. Large
- * two-array lattices with all options automatic take two steps per launch
+/* Enqueues n fused pull steps (Algorithm 3). n = 0 is a no-op. Large and
+ * small two-array lattices with all options automatic take two steps per launch
  * where n allows it (not while per-step timing is on, not across a finite
  * check); the state is the same bit for bit.
  * Errors: LBM_ERR_INVALID for n < 0; LBM_ERR_STATE after a device error;

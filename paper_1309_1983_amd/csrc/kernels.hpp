@@ -75,6 +75,14 @@ hipError_t launch_step_pair(int storage, int force_mode, const void* a, void* b,
                             const PairShape& ps, bool walls, bool moving, bool onsite, hipStream_t s,
                             const void** name = nullptr);
 
+// Two AB steps in one launch on a small lattice (kernels_box.hip): a
+// work-group computes a box of BOX_X x BOX_Y x BOX_Z points. Any storage
+// and force; walls: the lattice has solid points (no on-site nodes).
+constexpr int BOX_X = 16, BOX_Y = 4, BOX_Z = 2;
+hipError_t launch_step_box(int storage, int force_mode, const void* a, void* b, const uint8_t* flags,
+                           const uint32_t* smask, const uint32_t* mmask, const float* ffield, const StepArgs& args,
+                           bool walls, hipStream_t s);
+
 // The kernel (host-side function pointer) that launch_step_abv (vector) or
 // launch_step would launch with these arguments, without launching it.
 hipError_t resolve_step_kernel(bool vector, int storage, int pattern, int parity, int vw, bool collide,

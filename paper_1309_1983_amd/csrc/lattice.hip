@@ -83,6 +83,7 @@ struct lbm_lattice {
     bool pair = false;             // AB steps are taken two per launch where possible
     lbmk::PairShape pair_shape{};
     bool stream_stores = false;    // one-point AB step stores with the non-temporal hint
+    bool box = false;              // two steps per launch through boxes in LDS (small lattices)
     bool walls = false, moving = false;   // has solid points / moving ones
     unsigned shmem4 = 0;           // LDS reserved per vector-step work-group (residency cap)
     hipEvent_t order_ev = nullptr; // orders work across lbm_set_stream
@@ -210,6 +211,9 @@ bool takes_pairs(const lbm_lattice* L)
            (L->storage == LBM_STORAGE_F32 || force_mode(L) != lbmk::FORCE_UNIFORM) &&
            (!L->onsite || force_mode(L) == lbmk::FORCE_NONE);
 }
+
+// The same for the box kernel of small lattices.
+bool takes_boxes(const lbm_lattice* L) { return L->box && L->events.empty() && L->check_interval != 1; }
 
 lbmk::Launch launch_of(const lbm_lattice* L) { return lbmk::make_launch(L->dims, L->bx, L->by, L->stream); }
 
@@ -855,7 +859,13 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             lbm_destroy(L);
             return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
         }
-        L->pair = plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, cus, L->pair_shape);
+        // small lattices: where every box has a compute unit of its own (us per
+        // step, one step per launch / boxes: 256 boxes of 32^3 3.72 / 2.79; 486
+        // of 36^3 5.02 / 5.01, 350 of 100x20x19 3.75 / 4.68)
+        const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
+        L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
+                                   (unsigned long long)cus;
+        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, cus, L->pair_shape);
         L->pair_shape.stream = L->stream_stores ? 1u : 0u;
     }
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
@@ -1444,7 +1454,7 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
         HIPCHK(L, hipEventRecord(L->events[0], L->stream));
         L->ev_recorded = 1;
     }
-    const bool pairs = collide && takes_pairs(L);
+    const bool pairs = collide && (L->box ? takes_boxes(L) : takes_pairs(L));
     // arrays of the launch whose first step is s / whose last step is s
     auto in = [&](int s) { return s == 0 && from ? from : L->d_f[L->cur]; };
     auto out = [&](int s) { return s == n - 1 && to ? to : L->d_f[L->cur ^ 1]; };
@@ -1453,7 +1463,11 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
         // rho and u or a finite check is due in between
         if (pairs && n - s >= 2 && !(rho && n - s == 2) &&
             (L->check_interval == 0 || (L->steps_done + 1) % L->check_interval != 0)) {
-            HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
+            if (L->box)
+                HIPCHK(L, lbmk::launch_step_box(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
+                                                L->d_force, args, L->walls, L->stream));
+            else
+                HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
                                              L->d_force, args, L->pair_shape, L->walls, L->moving, L->onsite, L->stream));
             L->cur ^= 1;
             L->steps_done += 2;
