@@ -86,6 +86,7 @@ struct lbm_lattice {
     bool box = false;              // two steps per launch through boxes in LDS (small lattices)
     bool walls = false, moving = false;   // has solid points / moving ones
     unsigned shmem4 = 0;           // LDS reserved per vector-step work-group (residency cap)
+    unsigned shmem1 = 0;           // the same for the one-point step
     hipEvent_t order_ev = nullptr; // orders work across lbm_set_stream
 
     bool sticky = false;
@@ -585,6 +586,7 @@ bool one_point(const lbm_lattice* L, double near_fraction)
 // wave each): 256^3 cavity on MI355X, 426 us per step at the 12 that the
 // kernel's registers allow, 412 us at 8, 415 us at 10, 438 us at 5.
 constexpr int AUTO_GROUPS_PER_CU_F32 = 8;
+constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 
 // Tiling of the two-step kernel for an nx x ny x nz lattice, and whether two
 // steps in one launch take less time than two launches of one step.
@@ -876,7 +878,18 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     if (cap == 0)
         cap = (L->cpl > 1 && L->storage == LBM_STORAGE_F32 && !L->early && opt.block_x == 0 && opt.block_y == 0)
                   ? AUTO_GROUPS_PER_CU_F32 : -1;
-    if (cap > 0 && L->cpl > 1) {
+    // and of the FP32 one-point steps, where the arrays exceed the memory-side
+    // cache: five groups of 192 or 256 (MI355X, us per step, as many as fit / five: in
+    // place 256^3 468 / 452, 192^3 208 / 200, but 128^3, 159 MB, 49.6 / 50.1; two
+    // arrays 256^3 cavity 434 / 412, storing rho and u 256^3 sphere duct 540 / 515,
+    // 149x149x239 duct 252 / 224, 192^3 231 / 222; 16-bit
+    // steps need all their waves, 256^3 FP16 219 / 300)
+    const int items = L->bx * L->by;
+    const bool few_waves = L->cpl == 1 && (items == 256 || items == 192) && opt.block_x == 0 && opt.block_y == 0;
+    const bool large = fbytes * (L->pattern == LBM_PATTERN_AB ? 2 : 1) > ((size_t)256 << 20);
+    const bool cap_one = opt.groups_per_cu == 0 && L->storage == LBM_STORAGE_F32 && few_waves && large;
+    if (cap_one) cap = AUTO_GROUPS_PER_CU_ONE_F32;
+    if (cap > 0 && (L->cpl > 1 || cap_one)) {
         int lds_cu = 0, lds_block = 0;
         hipError_t e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
@@ -891,7 +904,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             return fail(LBM_ERR_INVALID, "groups_per_cu = %d cannot be set with %d bytes of LDS per compute unit", cap,
                         lds_cu);
         }
-        L->shmem4 = sh;
+        (L->cpl > 1 ? L->shmem4 : L->shmem1) = sh;
     }
     *out = L;
     return LBM_OK;
@@ -1446,7 +1459,8 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
 {
     if (n == 0) return LBM_OK;
     const lbmk::StepArgs args = step_args(L);
-    const lbmk::Launch LA = launch_of(L);
+    lbmk::Launch LA = launch_of(L);
+    LA.shmem = L->shmem1;
     const lbmk::Launch LA4 = L->cpl > 1 ? launch4_of(L) : LA;
     const int fm = collide ? force_mode(L) : lbmk::FORCE_NONE;
     const long long R = (long long)L->events.size();
