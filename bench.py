@@ -41,9 +41,14 @@ MACROS_BYTES = 16   # rho and u stored every step (Section 4.1: 152 -> 168 B)
 FORCE_FIELD_BYTES = 12   # a per-point force [3][N] FP32 read by every step
 # reverse step: reads b 76, s 76 and F 12; writes b 76; grad_F read and written 24
 ADJOINT_REVERSE_BYTES = 264
-# per point and time step of the reverse sweep: the recompute step with the
-# force field (152 + 12) plus the reverse step
-ADJOINT_BYTES_PER_POINT = BYTES_PER_POINT["f32"] + FORCE_FIELD_BYTES + ADJOINT_REVERSE_BYTES
+
+
+def adjoint_bytes_per_point(T, K):
+    """Per point and time step of a reverse sweep: the reverse step, and the
+    steps with the force field that recompute the states between checkpoints
+    of every segment but the last, whose states the rollout kept."""
+    recomputed = ((T + K - 1) // K - 1) * (K - 1)
+    return ADJOINT_REVERSE_BYTES + (BYTES_PER_POINT["f32"] + FORCE_FIELD_BYTES) * recomputed / T
 
 
 def log(msg):
@@ -755,10 +760,11 @@ def main():
         for key, an, T, K in (("adjoint", n, 200, 50), ("adjoint64", 64, 200, 20)):
             try:
                 ar, gb = adjoint_rate(torch, an, T=T, K=K, tau=0.7)
-                gbs = ar * 1e6 * ADJOINT_BYTES_PER_POINT / 1e9
+                bpp = adjoint_bytes_per_point(T, K)
+                gbs = ar * 1e6 * bpp / 1e9
                 extra[key] = {"mlups": round(ar, 1), "T": T, "K": K, "device_gb": round(gb, 2),
                               "workload": f"duct {an}^3, per-point force, tau 0.7",
-                              "bytes_per_point": ADJOINT_BYTES_PER_POINT, "gbs_alg": round(gbs, 1),
+                              "bytes_per_point": round(bpp, 1), "gbs_alg": round(gbs, 1),
                               "frac": round(gbs / HBM_PEAK_GBS, 4)}
                 if an <= 64:
                     extra[key]["note"] = "20 MB states: largely cache-resident, no roofline claim"

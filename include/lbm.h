@@ -96,19 +96,19 @@ typedef struct lbm_options {
     int check_interval;   /* > 0: lbm_step checks for non-finite values every
                              this many steps (synchronises the stream) */
     int device;           /* HIP device ordinal; -1 = the current device */
-    int cells_per_lane;   /* AB step: points per work-item. 0 = automatic (8
-                             for 16-bit storage when nx % 8 == 0 and either
-                             nx >= 256 or at least 8% of the fluid points have
-                             a solid neighbour, else 4 when nx % 4 == 0,
-                             else 1; 1 for lattices of at most 2^18 points
-                             without solid points; bfloat16 steps taken while
-                             a body force is set use 4 where the automatic
-                             choice is 8);
+    int cells_per_lane;   /* AB step: points per work-item. 0 = automatic (one
+                             where that is faster: nearly all 16-bit lattices
+                             with walls, FP32 ones of up to 5e6 points, porous
+                             ones and small periodic ones; otherwise 4, or 8 for
+                             16-bit storage when nx % 8 == 0 and nx >= 256 or at
+                             least 8% of the fluid points have a solid
+                             neighbour; and two steps per launch on large and on
+                             small lattices, see lbm_step);
                              1; 4; or 8 (16-bit storage only: 16-byte
                              accesses). 4 and 8 need
                              nx to be a multiple of them and
                              block_x * block_y <= 256 (block_x then counts
-                             work-items) */
+                             work-items). Results are identical. */
     int gather_mode;      /* FP32 multi-point AB step: 0 = automatic (early
                              gather when at least 8% of the fluid points have a
                              solid neighbour), 1 = flags first, 2 = early
@@ -117,7 +117,8 @@ typedef struct lbm_options {
     int groups_per_cu;    /* multi-point AB step: work-groups resident per
                              compute unit. 0 = automatic (8 for FP32 storage
                              with the default work-group shape when the flags
-                             come first, else as many as the registers allow),
+                             come first, else as many as the registers allow;
+                             5 for FP32 one-point steps on large lattices),
                              -1 = as many as the registers allow, 1..64 = that
                              cap (LDS is reserved per work-group, never used).
                              Results are identical. */

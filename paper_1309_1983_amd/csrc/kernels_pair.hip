@@ -9,6 +9,15 @@
 // s^{t+2} of the tile one plane behind: per two steps the state is read and
 // written once. The halo is computed again by the neighbouring tiles.
 //
+// MI355X, us per step, one step per launch / this: 256^3 FP32 cavity 407 / 278,
+// periodic 434 / 262, sphere duct 128x128x256 114 / 91, 256^3 FP16 periodic 261
+// / 190. What bounds it: a plane's loads and stores, 256 of the 278 us with the
+// arithmetic taken out; the arithmetic and LDS exchange alone take 99 to 114.
+// Reads from memory are 1.13 to 1.35 times the state (the halo rows of
+// neighbouring tiles that miss L2), writes exact. Tiles of 64 columns make a wave's stores one row; one
+// work-group of 16 waves per compute unit, because halving it would double the
+// halo, and 128 registers per work-item leave room for no second one.
+//
 // Per point both steps do the arithmetic of the one-step kernels on values
 // rounded to the storage format in between, so the result is the same bit for
 // bit.
@@ -195,7 +204,7 @@ __device__ __forceinline__ void pair_march(const typename St::bits_t* __restrict
 
     for (int it = 0; it < depth + 2; ++it) {
         const int zt = z0 - 1 + it;   // plane of s^{t+1}
-        rebuild(m0);   // before the loads, whose registers it can use
+        rebuild(m0);   // before the loads, whose registers it can use (after them 5 spill, 256^3 361 -> 378 us)
         uint32_t sm2 = 0, v2 = 0, fl3 = 0;
         // the wave issues its loads at raised priority: they get into the
         // memory pipeline before other waves' arithmetic (3% on the cavity)

@@ -7,8 +7,10 @@ namespace lbmk {
 
 // ---------------------------------------------------------------------------
 // AB pull step, one point per work-item: gather from x - e_i in `src`,
-// bounce back at solid neighbours, collide, store into `dst`. Used when the
-// row length is not a multiple of the vector width. MACROS: also store the
+// bounce back at solid neighbours, collide, store into `dst`. Used where it is
+// faster than several points per work-item (bound by its 38 accesses per point:
+// 28 waves per compute unit keep more of them in flight than the vector step's
+// 8 to 12), and where rows do not divide into vectors. MACROS: also store the
 // in-step rho and u (the four extra stores per point of Section 4.1).
 // ONSITE: rebuild the unknown populations of on-site velocity nodes.
 // Solid points of a wave that holds fluid points are stored as the rest state,

@@ -1,7 +1,9 @@
 // Forward kernels for gfx950: the fused pull step (Mawson & Revell, Section 4.2,
-// Algorithm 3) in the two-array (AB) pattern and the single-array (AA)
-// pattern, plus the auxiliary per-point kernels (initialisation, macroscopic
+// Algorithm 3) in the two-array (AB) pattern with several points per
+// work-item, plus the auxiliary per-point kernels (initialisation, macroscopic
 // output, state copy in and out, finite check, flag preprocessing, copy probe).
+// One point per work-item and the single-array (AA) pattern: kernels_point.hip;
+// two steps per launch: kernels_pair.hip and kernels_box.hip.
 //
 // Work-groups are x-dominant (Section 6) and every work-group lies in one
 // z-slab. Populations are stored per (direction, slab) plane (see plane() in

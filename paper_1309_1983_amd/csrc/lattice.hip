@@ -543,10 +543,10 @@ d3q19::Dims dims_of(int nx, int ny, int nz)
 // Porous geometry: at least this fraction of the fluid points have a solid
 // neighbour. There the FP32 AB step gathers before the flag branches (sphere
 // duct, 10%: 126.7 -> 114.1 us per step; 256^3 cavity, 2%: 3% slower) and
-// the 16-bit AB step takes eight points per work-item when rows allow it
-// (sphere duct 128 x 128 x 256: FP16 77.0 -> 69.1 us, BF16 79.4 -> 73.8 us;
-// the plain 128-wide duct, 3%, is 1-6% faster with four). Bfloat16 steps
-// taken while a body force is set still launch four (vec_shape).
+// the 16-bit AB step, where it is not one point per work-item (one_point), takes
+// eight when rows allow it (sphere duct 128 x 128 x 256: FP16 77.0 -> 69.1 us,
+// BF16 79.4 -> 73.8 us; the plain 128-wide duct, 3%, is 1-6% faster with four).
+// Bfloat16 steps taken while a body force is set then launch four (vec_shape).
 constexpr double POROUS_MIN_NEAR_FRACTION = 0.08;
 // Lattices without solid points up to this size step with one point per
 // work-item when the width is automatic.
@@ -559,7 +559,7 @@ constexpr size_t SMALL_PERIODIC_MAX_POINTS = (size_t)1 << 18;
 // issues fewer memory instructions, which counts once the lattice is large.
 // MI355X, us per step, one point / best of several:
 //  FP32: cavity 64^3 8.9 / 9.5, 96^3 22.7 / 32.1, 144^3 82.7 / 88.1, 176^3 145
-//  / 151, 192^3 189 / 178, 256^3 436 / 409; periodic 80^3 14.0 / 16.7, 128^3
+//  / 151, 192^3 189 / 178, 256^3 436 / 409 (412 with the residency cap); periodic 80^3 14.0 / 16.7, 128^3
 //  55 / 60, 192^3 187 / 181; sphere duct 128x128x256 111 / 113, 256^3 444 /
 //  461; on-site walls 132x131x131 78 / 83, 128^3 57 / 70, 260x259x259 554 / 571.
 //  16 bits: cavity 64^3 6.4 / 10.7, 128^3 28 / 33, 192^3 96 / 104, 256^3 219 /
@@ -882,8 +882,8 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     // cache: five groups of 192 or 256 (MI355X, us per step, as many as fit / five: in
     // place 256^3 468 / 452, 192^3 208 / 200, but 128^3, 159 MB, 49.6 / 50.1; two
     // arrays 256^3 cavity 434 / 412, storing rho and u 256^3 sphere duct 540 / 515,
-    // 149x149x239 duct 252 / 224, 192^3 231 / 222; 16-bit
-    // steps need all their waves, 256^3 FP16 219 / 300)
+    // 149x149x239 duct 252 / 224, 192^3 231 / 222; 16-bit steps need all their
+    // waves, 256^3 FP16 219 / 300)
     const int items = L->bx * L->by;
     const bool few_waves = L->cpl == 1 && (items == 256 || items == 192) && opt.block_x == 0 && opt.block_y == 0;
     const bool large = fbytes * (L->pattern == LBM_PATTERN_AB ? 2 : 1) > ((size_t)256 << 20);
