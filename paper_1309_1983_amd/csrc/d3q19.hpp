@@ -191,22 +191,37 @@ struct Dims {
     uint32_t nxy;   // nx*ny
     uint32_t N;     // nx*ny*nz (< 2^30)
     uint32_t flat;  // one-point kernels: 1 = one-dimensional grid over the points of a plane
+    uint32_t xcd;   // one-point kernels: 1 = each XCD takes consecutive work-groups
 };
 
 // The point of this work-item in a launch of one point per work-item; false
 // outside the plane. Rows that are not a multiple of a wave run on a
 // one-dimensional grid over the plane, so that every wave is full.
-__device__ __forceinline__ bool point_of(const Dims& d, int& x, int& y)
+// Work-groups go to the 8 XCDs in turn. With d.xcd the XCD k = g % 8 takes the
+// groups of the k-th eighth of the lattice in place of every eighth group: its
+// points' neighbours, and their values of the step before, are then largely in
+// its own L2.
+__device__ __forceinline__ bool point_of(const Dims& d, int& x, int& y, uint32_t& z)
 {
+    uint32_t bx = blockIdx.x, by = blockIdx.y;
+    z = blockIdx.z;
+    if (d.xcd) {
+        const uint32_t plane = gridDim.x * gridDim.y, n = plane * gridDim.z;
+        const uint32_t g = bx + gridDim.x * (by + gridDim.y * z), k = g & 7u;
+        const uint32_t t = k * (n >> 3) + min(k, n & 7u) + (g >> 3);
+        z = t / plane;
+        by = (t - z * plane) / gridDim.x;
+        bx = t - z * plane - by * gridDim.x;
+    }
     if (d.flat) {
-        const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
+        const uint32_t k = bx * blockDim.x + threadIdx.x;
         const uint32_t row = k / (uint32_t)d.nx;
         y = (int)row;
         x = (int)(k - row * (uint32_t)d.nx);
         return k < d.nxy;
     }
-    x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    y = (int)(blockIdx.y * blockDim.y + threadIdx.y);
+    x = (int)(bx * blockDim.x + threadIdx.x);
+    y = (int)(by * blockDim.y + threadIdx.y);
     return x < d.nx && y < d.ny;
 }
 

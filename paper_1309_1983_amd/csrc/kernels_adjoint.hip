@@ -46,8 +46,8 @@ __global__ __launch_bounds__(1024) void k_adj_seed(const float* __restrict__ f,
 {
     const Dims& d = a.d;
     int x, y;
-    if (!point_of(d, x, y)) return;
-    const uint32_t z = blockIdx.z;
+    uint32_t z;
+    if (!point_of(d, x, y, z)) return;
     const uint32_t o = (uint32_t)y * (uint32_t)d.nx + (uint32_t)x;
     const uint32_t c = z * d.nxy + o;
     const size_t N = d.N;
@@ -188,8 +188,8 @@ __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
     constexpr bool FORCE = FM != FORCE_NONE;
     const Dims& d = a.d;
     int x, y;
-    const bool inside = point_of(d, x, y);
-    const uint32_t z = blockIdx.z;
+    uint32_t z;
+    const bool inside = point_of(d, x, y, z);
     const uint32_t o = inside ? (uint32_t)y * (uint32_t)d.nx + (uint32_t)x : 0u;
     const uint32_t c = z * d.nxy + o;
     const uint8_t fl = inside ? flags[c] : (uint8_t)1;

@@ -303,6 +303,28 @@ lbmk::Launch adjoint_launch(const d3q19::Dims& dims, bool vec_ok, hipStream_t st
     return lbmk::make_launch(q, abx, aby, stream);
 }
 
+// Whether the one-point kernels give each XCD an eighth of the lattice
+// (point_of): where the arrays fit the memory-side cache, an XCD's L2 then
+// holds much of what its next step reads. MI355X, us per step, groups in turn /
+// eighths: FP32 cavity 48^3 6.96 / 5.66, 96^3 22.7 / 21.3, 112^3 36.2 / 32.2,
+// 120^3 (263 MB) 46.8 / 45.6; FP16 cavity 96^3 16.7 / 15.0, 144^3 41.9 / 38.3;
+// in place FP32 144^3 78.8 / 69.6. Beyond the cache it loses DRAM page locality:
+// 128^3 FP32 53.1 / 57.7, 144^3 82.1 / 83.8. Planes of a multiple of 8 KB lie on
+// the same memory channels in all eighths: 64^3 FP16 6.35 / 6.66, in place 6.61 /
+// 6.92, bfloat16 periodic 5.61 / 6.04, 128^3 FP16 28.3 / 28.3; two FP32 arrays
+// still gain, 64^3 8.89 / 8.63.
+bool xcd_eighths(const lbm_lattice* L)
+{
+    const bool ab = L->pattern == LBM_PATTERN_AB, f32 = L->storage == LBM_STORAGE_F32;
+    const size_t plane = (size_t)L->dims.nxy * storage_bytes(L->storage);
+    return plane * Q * (size_t)L->nz * (ab ? 2 : 1) <= ((size_t)256 << 20) && (plane % 8192 != 0 || (ab && f32));
+}
+
+// The same for the launches of a rollout and its reverse sweep, whose states
+// pass through HBM: us per step of both, 48^3 24.7 / 23.3, 77x70x65 47.5 / 45.8,
+// but 96^3 91.5 / 92.7, 112^3 151 / 156.
+constexpr size_t XCD_TRAJECTORY_MAX_POINTS = (size_t)1 << 19;
+
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 size_t state_bytes_of(size_t N) { return (size_t)Q * N * sizeof(float); }
@@ -566,9 +588,11 @@ constexpr size_t SMALL_PERIODIC_MAX_POINTS = (size_t)1 << 18;
 //  225, 384x200x200 208 / 208, 512^3 1862 / 1758, 168^3 69 / 72 but 224^3 188 /
 //  160 (rows of 3.5 waves); sphere duct 128x128x256 59 / 63 (bfloat16 with a
 //  force 62.8 / 64.1); periodic 128^3 26 / 36, 256^3 217 / 250.
-// Lattices with hardly a solid point, FP32 periodic ones of more than 2^18
-// points with rows off the 64-byte lines, and small 16-bit ones with rows of
-// 256 points and more keep the several-point step: the tests of the automatic
+// FP32 periodic lattices with rows off the lines that the caches hold, 76x90x77
+// 13.9 / 22.7, 72x70x68 10.1 / 12.8.
+// Lattices with hardly a solid point, FP32 periodic ones with rows off the lines
+// of 2^18 to 300000 points or beyond the cache, and small 16-bit ones with rows
+// of 256 points and more keep the several-point step: the tests of the automatic
 // choice name it there (one point would be faster by 10-40%).
 bool one_point(const lbm_lattice* L, double near_fraction)
 {
@@ -578,7 +602,7 @@ bool one_point(const lbm_lattice* L, double near_fraction)
     const bool walls = near_fraction >= 0.01, porous = near_fraction >= POROUS_MIN_NEAR_FRACTION;
     if (!L->walls && N <= SMALL_PERIODIC_MAX_POINTS) return true;
     if (L->storage == LBM_STORAGE_F32)
-        return L->onsite || (porous && lines) || (N <= 5000000 && (L->walls ? walls : lines));
+        return L->onsite || (porous && lines) || (N <= 5000000 && (L->walls ? walls : lines || (L->dims.xcd && N > 300000)));
     if (nx >= 256 && N < (1u << 20)) return false;
     return !L->walls || (walls && N <= (3u << 20)) || (nx % 64 == 0 && nx < 512);
 }
@@ -596,8 +620,8 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 // times the planes that one of them computes (two more than it stores). The
 // times are MI355X measurements: a plane of 1024 work-items takes 6.0 us
 // (periodic 256^3), 6.4 us (walled duct, cavity) to 8 us (10%-solid sphere
-// duct) in FP32 and 4.3 us with 16-bit storage, a tenth less where both arrays
-// fit the memory-side cache, a fifth more where rows start anywhere on a line,
+// duct) in FP32 and 4.3 us with 16-bit storage, less where both arrays fit the
+// memory-side cache, a fifth more where rows start anywhere on a line,
 // and the first plane's loads 4 us. Two steps, pair against single kernels, us: cavity 256^3 555 / 813,
 // cavity 128^3 95 / 120, cavity 96^3 49 / 66, sphere duct 128x128x256 183 /
 // 228, periodic 256^3 FP16 381 / 522; but cavity 64^3 26 / 19: too few planes
@@ -614,17 +638,27 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 // pair: 132x131x131 77.7 / 67.8, 256^3 432 / 361, 182x193x490 656 / 537; but
 // 128^3 56.2 / 58.2, 160^3 107 / 124, 140x110x150 76 / 86, 139x131x131 (363 MB) 89 / 97,
 // 130x128x107 (271 MB) 48 / 52, 112^3 (213 MB) 39 / 46.
-bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, int cus, lbmk::PairShape& best)
+//
+// Where the one-point kernel gives each XCD an eighth of the lattice (xcd) it
+// reaches 7.2 TB/s from the caches (6.4 on rows off 16 bytes), us per step, pair
+// / single: cavity 88^3 18.4 / 16.9, 96^3 19.4 / 21.3, 100x110x90 22.4 / 24.5,
+// periodic 81^3 13.3 / 14.0. 16-bit lattices that the caches hold take single
+// steps: periodic FP16 112^3 19.3 / 18.1, 120^3 23.9 / 22.4, 144^3 35.9 / 35.1,
+// 128^3 25.6 / 26.3.
+bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, bool xcd, int cus,
+               lbmk::PairShape& best)
 {
     const bool f32 = storage == LBM_STORAGE_F32;
     if (!f32 && walls) return false;
-    if ((unsigned long long)nx * ny > (1ull << 28) || nx < 2) return false;
     const double N = (double)nx * ny * nz;
+    const bool cached = 2.0 * N * Q * (f32 ? 4 : 2) <= 256.0 * (1 << 20);
+    if (!f32 && cached) return false;
+    if ((unsigned long long)nx * ny > (1ull << 28) || nx < 2) return false;
     if (N < 524288.0) return false;   // a few planes per work-group at most
     // a single step: bytes at the rate its kernel reaches, plus its launch
     const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
     const bool lines = (size_t)nx * (f32 ? 4 : 2) % 64 == 0;   // rows start on 64-byte lines
-    const double rate = onsite ? (lines ? 5.8e6 : ((size_t)nx * ny % 16 == 0 ? 5.1e6 : 4.7e6))
+    const double rate = xcd ? (nx % 4 == 0 ? 7.2e6 : 6.4e6) : onsite ? (lines ? 5.8e6 : ((size_t)nx * ny % 16 == 0 ? 5.1e6 : 4.7e6))
                                : f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
     const double single = bytes / rate + 2.5;
     lbmk::PairShape ps{};
@@ -639,10 +673,12 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, int
     ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
-    const bool cached = 2.0 * N * Q * (f32 ? 4 : 2) < 256.0 * (1 << 20);
     if (onsite && bytes < (nx % 4 == 0 ? 320e6 : 400e6)) return false;   // largely held by the cache
     const double full = onsite ? 8.4 : f32 ? (walls ? 6.6 : 6.1) : 4.4;
-    const double plane = full * (cached ? 0.9 : (lines ? 1.0 : 1.2)) * std::max(0.5, ps.threads / 1024.0);
+    const double fill = ps.threads / 1024.0;
+    // from the cache a plane costs less, and not in proportion to its work-items
+    const double plane = cached ? (walls ? 3.5 + 1.4 * fill : 1.6 + 2.45 * fill)
+                                : full * (lines ? 1.0 : 1.2) * std::max(0.5, fill);
     // a few columns short of whole 64-byte lines: take them (us per step, before
     // / after: 140x110x150 cavity 47 columns 69.9 / 65.6, 292x192x401 59
     // columns 616 / 574, 245x216x126 periodic 62 columns 148 / 134)
@@ -665,7 +701,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, int
             best = ps;
         }
     }
-    return best.groups > 0 && least < 0.95 * 2.0 * single;
+    return best.groups > 0 && least < (cached ? 0.99 : 0.95) * 2.0 * single;
 }
 
 }  // namespace
@@ -758,6 +794,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     L->device = dev;
     L->storage = opt.storage;
     L->pattern = opt.pattern;
+    L->dims.xcd = xcd_eighths(L) ? 1u : 0u;
     L->bx = lay.bx; L->by = lay.by;
     L->stream = static_cast<hipStream_t>(opt.hip_stream);
     L->tau = tau;
@@ -867,7 +904,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
         const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
         L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
                                    (unsigned long long)cus;
-        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, cus, L->pair_shape);
+        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, L->dims.xcd != 0, cus, L->pair_shape);
         L->pair_shape.stream = L->stream_stores ? 1u : 0u;
     }
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
@@ -1409,6 +1446,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
     const lbmk::Launch LA = launch_of(L);
     const lbmk::StepArgs args = step_args(L);
     lbmk::StepArgs rargs = args;   // the reverse step has a launch shape of its own
+    rargs.d.xcd = args.d.xcd && L->N <= XCD_TRAJECTORY_MAX_POINTS ? 1u : 0u;
     rargs.d.flat = !vec && !wave_rows(L->nx) ? 1u : 0u;
     rargs.agx = vec && !wave_rows(L->nx / 2) ? (uint32_t)(L->nx / 2) : 0u;
     const int fm = force_mode(L);
@@ -1458,7 +1496,8 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
 lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, void* from, void* to)
 {
     if (n == 0) return LBM_OK;
-    const lbmk::StepArgs args = step_args(L);
+    lbmk::StepArgs args = step_args(L);
+    if ((from || to) && L->N > XCD_TRAJECTORY_MAX_POINTS) args.d.xcd = 0u;
     lbmk::Launch LA = launch_of(L);
     LA.shmem = L->shmem1;
     const lbmk::Launch LA4 = L->cpl > 1 ? launch4_of(L) : LA;

@@ -47,8 +47,8 @@ __device__ __forceinline__ Macro decode_collide(const typename St::raw_t raw[Q],
 
 #define POINT_PROLOGUE(d)                                                                      \
     int x, y;                                                                                  \
-    if (!point_of((d), x, y)) return;                                                          \
-    const uint32_t z = blockIdx.z;                                                             \
+    uint32_t z;                                                                                \
+    if (!point_of((d), x, y, z)) return;                                                       \
     const uint32_t o = (uint32_t)y * (uint32_t)(d).nx + (uint32_t)x;                           \
     const uint32_t c = z * (d).nxy + o;                                                        \
     const uint32_t zm = wrap_m(z, (uint32_t)(d).nz), zp = wrap_p(z, (uint32_t)(d).nz);

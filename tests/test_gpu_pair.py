@@ -42,13 +42,13 @@ CASES = [
     ((98, 110, 100), "duct", "f32", "field"),
     ((133, 90, 88), None, "f32", None),                   # periodic: row ends wrap
     ((64, 150, 110), None, "f32", "field"),               # one tile per row, wrapping onto itself
-    ((133, 100, 98), None, "f16", "field"),
-    ((144, 130, 98), None, "bf16", "field"),
-    ((66, 200, 100), None, "f16", None),
+    ((131, 130, 228), None, "f16", "field"),
+    ((128, 130, 228), None, "bf16", "field"),
+    ((66, 260, 228), None, "f16", None),
     ((132, 131, 131), "onsite", "f32", None),             # on-site nodes on faces, edges and corners
     ((223, 120, 100), "onsite", "f32", None),
     ((140, 110, 98), "cavity", "f32", None),              # 47 columns taken as 48
-    ((184, 130, 98), None, "f16", None),                  # 62 as 64
+    ((184, 130, 150), None, "f16", None),                  # 62 as 64
 ]
 
 
