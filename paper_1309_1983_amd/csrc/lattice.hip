@@ -1511,21 +1511,30 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
     // arrays of the launch whose first step is s / whose last step is s
     auto in = [&](int s) { return s == 0 && from ? from : L->d_f[L->cur]; };
     auto out = [&](int s) { return s == n - 1 && to ? to : L->d_f[L->cur ^ 1]; };
+    // Two steps in one launch, and such launches in twos, so that the arrays
+    // are swapped as often as the steps would: a graph of an even number of
+    // steps, or of the fields, finds the state in the array that it was
+    // captured with. Four steps are taken so unless the fourth is the one that
+    // stores rho and u or a finite check is due in between.
+    const int ci = L->check_interval;
+    auto four = [&](int s) {
+        return n - s >= 4 && !(rho && n - s == 4) && (ci == 0 || (L->steps_done % ci) + 4 <= ci);
+    };
     for (int s = 0; s < n; ++s) {
-        // two steps in one launch, unless the second is the one that stores
-        // rho and u or a finite check is due in between
-        if (pairs && n - s >= 2 && !(rho && n - s == 2) &&
-            (L->check_interval == 0 || (L->steps_done + 1) % L->check_interval != 0)) {
-            if (L->box)
-                HIPCHK(L, lbmk::launch_step_box(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
-                                                L->d_force, args, L->walls, L->stream));
-            else
-                HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
-                                             L->d_force, args, L->pair_shape, L->walls, L->moving, L->onsite, L->stream));
-            L->cur ^= 1;
-            L->steps_done += 2;
-            ++s;
-            if (L->check_interval > 0 && L->steps_done % L->check_interval == 0) {
+        if (pairs && four(s)) {
+            for (int h = 0; h < 2; ++h, s += 2) {
+                if (L->box)
+                    HIPCHK(L, lbmk::launch_step_box(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
+                                                    L->d_force, args, L->walls, L->stream));
+                else
+                    HIPCHK(L, lbmk::launch_step_pair(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
+                                                     L->d_force, args, L->pair_shape, L->walls, L->moving, L->onsite,
+                                                     L->stream));
+                L->cur ^= 1;
+                L->steps_done += 2;
+            }
+            --s;   // the loop's own increment
+            if (ci > 0 && L->steps_done % ci == 0) {
                 lbm_status st = lbm_check_finite(L);
                 if (st != LBM_OK) return st;
             }
