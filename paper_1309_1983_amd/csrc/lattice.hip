@@ -517,7 +517,10 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     else if (bx == 0 && by == 0 && !wave_rows(nx)) { bx = row; by = 1; }
     if (bx == 0 && by == 0) default_block(nx, bx, by);
     if (bx <= 0 || by <= 0 || bx * by > 1024) return fail(LBM_ERR_INVALID, "bad block shape %dx%d", bx, by);
-    if ((ny + by - 1) / by > 65535) return fail(LBM_ERR_INVALID, "ny/block_y must be <= 65535 work-groups");
+    // ny has the limit of the two-dimensional grid also on the one-dimensional one
+    int rows_per_group = by, unused = 0;
+    if (flat1) default_block(nx, unused, rows_per_group);
+    if ((ny + rows_per_group - 1) / rows_per_group > 65535) return fail(LBM_ERR_INVALID, "ny/block_y must be <= 65535 work-groups");
     if (opt.timing_capacity < 0 || opt.check_interval < 0) return fail(LBM_ERR_INVALID, "negative timing/check option");
     if (opt.cells_per_lane != 0 && opt.cells_per_lane != 1 && !lbmk::vector_width_ok(opt.storage, opt.cells_per_lane))
         return fail(LBM_ERR_INVALID, "cells_per_lane must be 0, 1, 4%s (got %d)",
