@@ -322,8 +322,26 @@ bool xcd_eighths(const lbm_lattice* L)
 
 // The same for the launches of a rollout and its reverse sweep, whose states
 // pass through HBM: us per step of both, 48^3 24.7 / 23.3, 77x70x65 47.5 / 45.8,
-// but 96^3 91.5 / 92.7, 112^3 151 / 156.
+// but 96^3 91.5 / 92.7, 112^3 151 / 156 (the recompute steps alone, T = 64, K = 8,
+// us of the whole: 96^3 6015 / 5950 in turn, 112^3 9840 / 9730).
 constexpr size_t XCD_TRAJECTORY_MAX_POINTS = (size_t)1 << 19;
+
+// Arguments and launches of the one-step kernels; trajectory: for a rollout or
+// its reverse sweep.
+struct StepLaunches {
+    lbmk::StepArgs args;
+    lbmk::Launch one, vec;   // one point, several points per work-item (if the lattice has the form)
+};
+StepLaunches step_launches(const lbm_lattice* L, bool trajectory)
+{
+    StepLaunches s;
+    s.args = step_args(L);
+    if (trajectory && L->N > XCD_TRAJECTORY_MAX_POINTS) s.args.d.xcd = 0u;
+    s.one = launch_of(L);
+    s.one.shmem = L->shmem1;
+    s.vec = L->cpl > 1 ? launch4_of(L) : s.one;
+    return s;
+}
 
 size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -1446,10 +1464,14 @@ namespace {
 lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2], double* part,
                          const lbmk::Launch& LR, bool vec)
 {
+    const StepLaunches sl = step_launches(L, true);
+    const lbmk::StepArgs& args = sl.args;
+    // Recompute steps run without the residency cap that the rollout's have
+    // (MI355X, us per rollout and sweep of 32 steps, K = 6, without / with: packed
+    // spheres 192^3 22130 / 22470, 256x128x160 16000 / 16200; the rollout's own
+    // steps without it 22580, 16370)
     const lbmk::Launch LA = launch_of(L);
-    const lbmk::StepArgs args = step_args(L);
     lbmk::StepArgs rargs = args;   // the reverse step has a launch shape of its own
-    rargs.d.xcd = args.d.xcd && L->N <= XCD_TRAJECTORY_MAX_POINTS ? 1u : 0u;
     rargs.d.flat = !vec && !wave_rows(L->nx) ? 1u : 0u;
     rargs.agx = vec && !wave_rows(L->nx / 2) ? (uint32_t)(L->nx / 2) : 0u;
     const int fm = force_mode(L);
@@ -1471,7 +1493,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
         for (int j = 1; j < len && L->seg_of != k; ++j) {
             if (L->cpl > 1)
                 HIPCHK(L, lbmk::launch_step_abv(LBM_STORAGE_F32, L->cpl, true, fm, state(j - 1), state(j), L->d_flags,
-                                                L->d_smask, L->d_mmask, L->d_force, args, launch4_of(L)));
+                                                L->d_smask, L->d_mmask, L->d_force, args, sl.vec));
             else
                 HIPCHK(L, lbmk::launch_step(LBM_STORAGE_F32, LBM_PATTERN_AB, 0, true, fm, state(j - 1), state(j),
                                             L->d_flags, L->d_smask, L->d_mmask, L->d_force, args, LA));
@@ -1499,11 +1521,8 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
 lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, void* from, void* to)
 {
     if (n == 0) return LBM_OK;
-    lbmk::StepArgs args = step_args(L);
-    if ((from || to) && L->N > XCD_TRAJECTORY_MAX_POINTS) args.d.xcd = 0u;
-    lbmk::Launch LA = launch_of(L);
-    LA.shmem = L->shmem1;
-    const lbmk::Launch LA4 = L->cpl > 1 ? launch4_of(L) : LA;
+    const StepLaunches sl = step_launches(L, from || to);
+    const lbmk::StepArgs& args = sl.args;
     const int fm = collide ? force_mode(L) : lbmk::FORCE_NONE;
     const long long R = (long long)L->events.size();
     if (R > 0 && L->ev_recorded == 0) {
@@ -1547,15 +1566,15 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
         float* mu = s == n - 1 ? u : nullptr;
         if (L->pattern == LBM_PATTERN_AB && L->cpl > 1) {
             HIPCHK(L, lbmk::launch_step_abv(L->storage, vec_shape(L).cpl, collide, fm, in(s), out(s), L->d_flags,
-                                            L->d_smask, L->d_mmask, L->d_force, args, LA4, mr, mu, L->onsite));
+                                            L->d_smask, L->d_mmask, L->d_force, args, sl.vec, mr, mu, L->onsite));
             L->cur ^= 1;
         } else if (L->pattern == LBM_PATTERN_AB) {
             HIPCHK(L, lbmk::launch_step(L->storage, 0, 0, collide, fm, in(s), out(s), L->d_flags,
-                                        L->d_smask, L->d_mmask, L->d_force, args, LA, mr, mu, L->onsite));
+                                        L->d_smask, L->d_mmask, L->d_force, args, sl.one, mr, mu, L->onsite));
             L->cur ^= 1;
         } else {
             HIPCHK(L, lbmk::launch_step(L->storage, 1, L->parity, collide, fm, L->d_f[0], nullptr, L->d_flags,
-                                        L->d_smask, L->d_mmask, L->d_force, args, LA, nullptr, nullptr,
+                                        L->d_smask, L->d_mmask, L->d_force, args, sl.one, nullptr, nullptr,
                                         L->onsite));
             L->parity ^= 1;
         }
