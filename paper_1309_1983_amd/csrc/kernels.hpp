@@ -36,6 +36,30 @@ struct Launch {
 
 Launch make_launch(const d3q19::Dims& d, int bx, int by, hipStream_t s);
 
+// The dimensions with what point_of needs to know of the launch; the launchers
+// of the one-point kernels call it on what they are given.
+inline d3q19::Dims on_grid(d3q19::Dims d, const Launch& L)
+{
+    const uint32_t n = L.grid.x * L.grid.y * L.grid.z;   // at most a group per point
+    d.bx = L.block.x;
+    d.by = L.block.y;
+    d.gx = L.grid.x;
+    d.gp = L.grid.x * L.grid.y;
+    d.mask = d.xcd ? 7u : 0u;
+    d.shift = d.xcd ? 3u : 0u;
+    d.eighth = n >> 3;
+    d.rest = n & 7u;
+    d.by_gx = d3q19::div_by(d.gx);
+    d.by_gp = d3q19::div_by(d.gp);
+    d.by_row = d.flat ? d3q19::div_by((uint32_t)d.nx) : d3q19::Div{0u, 32u};
+    return d;
+}
+inline StepArgs on_grid(StepArgs a, const Launch& L)
+{
+    a.d = on_grid(a.d, L);
+    return a;
+}
+
 // One step. AB: reads `a`, writes `b`. AA: in place on `a`; parity 0 is the
 // gather/scatter step, parity 1 the local step.
 // AB only: rho/u non-null also stores the in-step rho [N] and u [3][N].

@@ -421,13 +421,13 @@ hipError_t launch_adjoint_seed(int fm, const float* f, const uint8_t* flags, con
 {
     switch (fm) {
     case FORCE_UNIFORM:
-        hipLaunchKernelGGL((k_adj_seed<FORCE_UNIFORM>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, args);
+        hipLaunchKernelGGL((k_adj_seed<FORCE_UNIFORM>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, on_grid(args, L));
         break;
     case FORCE_FIELD:
-        hipLaunchKernelGGL((k_adj_seed<FORCE_FIELD>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, args);
+        hipLaunchKernelGGL((k_adj_seed<FORCE_FIELD>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, on_grid(args, L));
         break;
     default:
-        hipLaunchKernelGGL((k_adj_seed<FORCE_NONE>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, args);
+        hipLaunchKernelGGL((k_adj_seed<FORCE_NONE>), L.grid, L.block, L.shmem, L.stream, f, flags, ff, g, aout, gF, on_grid(args, L));
     }
     return hipGetLastError();
 }
@@ -438,9 +438,9 @@ static hipError_t adj_fm(bool direct, const float* s, const float* bin, float* b
                          const StepArgs& a, float it2, const Launch& L)
 {
     if (direct)
-        hipLaunchKernelGGL((k_adj_step<FM, true, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_step<FM, true, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, on_grid(a, L), it2);
     else
-        hipLaunchKernelGGL((k_adj_step<FM, false, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_step<FM, false, STREAM>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, on_grid(a, L), it2);
     return hipGetLastError();
 }
 

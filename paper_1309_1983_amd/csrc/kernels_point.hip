@@ -229,9 +229,10 @@ hipError_t launch_step(int storage, int pattern, int parity, bool collide, int f
                        const float* ffield, const StepArgs& args, const Launch& L, float* rho, float* u,
                        bool onsite)
 {
+    const StepArgs g = on_grid(args, L);
     return (onsite && collide)
-               ? step_os<true>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, args, L, rho, u)
-               : step_os<false>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, args, L, rho, u);
+               ? step_os<true>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, g, L, rho, u)
+               : step_os<false>(storage, pattern, parity, collide, force_mode, a, b, flags, smask, mmask, ffield, g, L, rho, u);
 }
 
 }  // namespace lbmk

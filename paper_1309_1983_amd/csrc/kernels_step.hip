@@ -535,7 +535,7 @@ hipError_t launch_step_abv(int storage, int vw, bool collide, int force_mode, vo
 hipError_t launch_mark_near_wall(const uint8_t* in, uint8_t* out, uint32_t* smask, uint32_t* mmask, int* bad,
                                  unsigned* counts, const Dims& d, const Launch& L)
 {
-    hipLaunchKernelGGL(k_mark_near_wall, L.grid, L.block, 0, L.stream, in, out, smask, mmask, bad, counts, d);
+    hipLaunchKernelGGL(k_mark_near_wall, L.grid, L.block, 0, L.stream, in, out, smask, mmask, bad, counts, on_grid(d, L));
     return hipGetLastError();
 }
 
@@ -543,7 +543,7 @@ template <class St>
 static hipError_t init_st(void* f, const float* rho, const float* u, const Dims& d, const Launch& L)
 {
     hipLaunchKernelGGL((k_init_eq<St>), L.grid, L.block, 0, L.stream,
-                       static_cast<typename St::raw_t*>(f), rho, u, d);
+                       static_cast<typename St::raw_t*>(f), rho, u, on_grid(d, L));
     return hipGetLastError();
 }
 
@@ -563,9 +563,9 @@ static hipError_t get_st(int layout, const void* f, const uint8_t* flags, float*
 {
     using T = typename St::raw_t;
     if (layout)
-        hipLaunchKernelGGL((k_get<St, 1>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, out, d);
+        hipLaunchKernelGGL((k_get<St, 1>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, out, on_grid(d, L));
     else
-        hipLaunchKernelGGL((k_get<St, 0>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, out, d);
+        hipLaunchKernelGGL((k_get<St, 0>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, out, on_grid(d, L));
     return hipGetLastError();
 }
 
@@ -582,7 +582,7 @@ hipError_t launch_get(int storage, int layout, const void* f, const uint8_t* fla
 template <class St>
 static hipError_t set_st(void* f, const float* in, const Dims& d, const Launch& L)
 {
-    hipLaunchKernelGGL((k_set<St>), L.grid, L.block, 0, L.stream, static_cast<typename St::raw_t*>(f), in, d);
+    hipLaunchKernelGGL((k_set<St>), L.grid, L.block, 0, L.stream, static_cast<typename St::raw_t*>(f), in, on_grid(d, L));
     return hipGetLastError();
 }
 
@@ -603,13 +603,13 @@ static hipError_t macros_l(int fm, const void* f, const uint8_t* flags, const fl
     const T* F = static_cast<const T*>(f);
     switch (fm) {
     case FORCE_UNIFORM:
-        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_UNIFORM>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, a);
+        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_UNIFORM>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, on_grid(a, L));
         break;
     case FORCE_FIELD:
-        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_FIELD>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, a);
+        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_FIELD>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, on_grid(a, L));
         break;
     default:
-        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_NONE>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, a);
+        hipLaunchKernelGGL((k_macros<St, LAYOUT, FORCE_NONE>), L.grid, L.block, 0, L.stream, F, flags, ff, rho, u, on_grid(a, L));
     }
     return hipGetLastError();
 }
@@ -638,9 +638,9 @@ static hipError_t finite_st(int layout, const void* f, const uint8_t* flags, int
 {
     using T = typename St::raw_t;
     if (layout)
-        hipLaunchKernelGGL((k_check_finite<St, 1>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, flag, d);
+        hipLaunchKernelGGL((k_check_finite<St, 1>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, flag, on_grid(d, L));
     else
-        hipLaunchKernelGGL((k_check_finite<St, 0>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, flag, d);
+        hipLaunchKernelGGL((k_check_finite<St, 0>), L.grid, L.block, 0, L.stream, static_cast<const T*>(f), flags, flag, on_grid(d, L));
     return hipGetLastError();
 }
 
