@@ -1300,6 +1300,7 @@ lbm_status lbm_forward_checkpointed(lbm_lattice* L, int T, int K)
     // the segment store, where the reverse sweep wants them first.
     const bool copies = L->check_interval > 0;
     const size_t floats = (size_t)Q * L->N;
+    const int last = L->cur ^ (T & 1);   // where T single steps leave the state
     for (int k = 0; k < nck && st == LBM_OK; ++k) {
         void* from = nullptr;
         if (k == 0 || copies)
@@ -1314,6 +1315,9 @@ lbm_status lbm_forward_checkpointed(lbm_lattice* L, int T, int K)
         }
         for (int j = 0; j < len && st == LBM_OK; ++j) {
             float* to = j + 1 < len ? L->d_seg + (size_t)j * floats : nullptr;
+            // the last step stores into array `last` (its input, unless it is the
+            // only one, lies outside the two)
+            if (!to) L->cur = last ^ 1;
             st = run_steps(L, 1, true, nullptr, nullptr, from, to);
             from = to;
         }
@@ -1536,15 +1540,13 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
     // Two steps in one launch, and such launches in twos, so that the arrays
     // are swapped as often as the steps would: a graph of an even number of
     // steps, or of the fields, finds the state in the array that it was
-    // captured with. Four steps are taken so unless the fourth is the one that
-    // stores rho and u or a finite check is due in between.
-    const int ci = L->check_interval;
-    auto four = [&](int s) {
-        return n - s >= 4 && !(rho && n - s == 4) && (ci == 0 || (L->steps_done % ci) + 4 <= ci);
-    };
+    // captured with. (Not with `to`: the state ends outside the two arrays.)
+    // Single steps where the last of the four is the one that stores rho and u
+    // or a finite check is due in between.
+    const int ci = L->check_interval, unit = to ? 2 : 4;
     for (int s = 0; s < n; ++s) {
-        if (pairs && four(s)) {
-            for (int h = 0; h < 2; ++h, s += 2) {
+        if (pairs && n - s >= unit && !(rho && n - s == unit) && (ci == 0 || L->steps_done % ci + unit <= ci)) {
+            for (const int end = s + unit; s < end; s += 2) {
                 if (L->box)
                     HIPCHK(L, lbmk::launch_step_box(L->storage, fm, in(s), out(s + 1), L->d_flags, L->d_smask, L->d_mmask,
                                                     L->d_force, args, L->walls, L->stream));

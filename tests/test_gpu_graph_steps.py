@@ -93,3 +93,38 @@ def test_fields_captured_once_follow_the_steps(shape, n):
             assert torch.equal(rho, r) and torch.equal(u, v), k
             stream.synchronize()
         lat.close()
+
+
+@pytest.mark.parametrize("shape", [(32, 20, 18), (128, 128, 64)])
+@pytest.mark.parametrize("T,K", [(1, 1), (2, 1), (2, 5), (5, 5), (6, 3), (12, 6), (13, 6), (14, 6)])
+def test_rollouts_end_in_the_array_that_single_steps_end_in(shape, T, K):
+    """The fields after a rollout, read by a graph captured before it: after
+    one of an even number of steps, or after two of an odd number."""
+    from paper_1309_1983_amd import Lattice
+    N = int(np.prod(shape))
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        one = Lattice(*shape, 0.7, stream=stream, cells_per_lane=1)   # one step per launch
+        lat = Lattice(*shape, 0.7, stream=stream)
+        assert ("k_step_pair<" in lat.step_kernel_name()) == (shape == (128, 128, 64))
+        s0 = torch.from_numpy(near_rest_state(N, 6))
+        for x in (one, lat):
+            x.set_populations(s0)
+        lat.macros()
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            rho, u = lat.macros()
+        for _ in range(3):
+            for _ in range(1 + T % 2):
+                lat.forward_checkpointed(T, K)
+                one.step(T)
+            g.replay()
+            r, v = one.macros()
+            assert torch.equal(rho, r) and torch.equal(u, v)
+            r, v = lat.macros()
+            assert torch.equal(rho, r) and torch.equal(u, v)
+            stream.synchronize()
+        lat.close()
+        one.close()
