@@ -77,10 +77,8 @@ typedef enum lbm_storage {
     LBM_STORAGE_BF16 = 2   /* bfloat16 offsets */
 } lbm_storage;
 
-/* AB: two population arrays, swapped after every step (Section 4.1): an even
- *     number of steps leaves the state in the array that held it (steps that
- *     are taken two per launch are taken in fours), so that a HIP graph that
- *     captured them advances the flow at every replay.
+/* AB: two population arrays, swapped after every launch of a step kernel: after
+ *     every step (Section 4.1), or after two where lbm_step takes two per launch.
  * AA: one array updated in place by alternating a gather/scatter step and a
  *     local step (each work-item reads and writes the same 19 slots). */
 typedef enum lbm_pattern {
@@ -221,7 +219,7 @@ lbm_status lbm_set_stream(lbm_lattice* lat, void* hip_stream);
 /* Name of the device kernel the next lbm_step launches (the fused step of
  * Algorithm 3 in the variant the lattice's storage, pattern, parity, force
  * and geometry select; on lattices whose steps are taken two per launch, the
- * two-step kernel, which lbm_step launches for n >= 4; small lattices, whose
+ * two-step kernel, which lbm_step launches for n >= 2; small lattices, whose
  * pairs of steps run on boxes in local memory, report the kernel of a single
  * step), as the HIP runtime reports it, demangled; written to buf
  * (NUL-terminated, truncated to cap bytes). For measurement tools that match
@@ -252,10 +250,13 @@ lbm_status lbm_set_force_field(lbm_lattice* lat, const float* F_dev);
 lbm_status lbm_init_equilibrium(lbm_lattice* lat, const float* rho_dev, const float* u_dev);
 
 /* Enqueues n fused pull steps (Algorithm 3). n = 0 is a no-op. Large and
- * small two-array lattices with all options automatic take four steps at a time
- * in two launches of two (not while per-step timing is on, not across a finite
- * check), and the n % 4 left over one per launch; the state is the same bit for
- * bit, and so is the array that holds it.
+ * small two-array lattices with all options automatic take two steps per launch
+ * where n allows it (not while per-step timing is on, not across a finite
+ * check); the state is the same bit for bit. Steps may be captured into a HIP
+ * graph: a graph of an even number of steps advances the flow at every replay.
+ * For that, once a call on the lattice has been captured, an even number of
+ * steps always ends in the array that held the state: launches of two steps
+ * then come in twos, and the n % 4 left over are taken one per launch.
  * Errors: LBM_ERR_INVALID for n < 0; LBM_ERR_STATE after a device error;
  * LBM_ERR_NONFINITE when a due check (check_interval) finds NaN/Inf. */
 lbm_status lbm_step(lbm_lattice* lat, int n);

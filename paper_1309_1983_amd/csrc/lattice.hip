@@ -67,6 +67,7 @@ struct lbm_lattice {
     bool own_f = true;             // population arrays allocated by the library
     int cur = 0;      // AB: index of the array holding the state
     int parity = 0;   // AA: 0 natural layout, 1 shifted layout
+    bool captured = false;         // a HIP graph may hold calls on the lattice (note_capture)
     uint8_t* d_flags = nullptr;
     uint32_t* d_smask = nullptr;   // solid-neighbour bits per cell
     uint32_t* d_mmask = nullptr;   // moving-wall-neighbour bits per cell
@@ -441,6 +442,22 @@ lbm_status hold_trajectory(lbm_lattice* L, int nck, int nseg)
     }
     if (st != LBM_OK) drop_trajectory(L);
     return st;
+}
+
+// Notes that the lattice's stream is being captured; called before anything is
+// enqueued that reads or writes the state. From then on the state lies in the
+// array that single steps would leave it in: a graph of an even number of
+// steps, or of the fields, finds it where it was when captured. Lattices that
+// take one step per launch do so anyway; the null stream cannot be captured.
+void note_capture(lbm_lattice* L)
+{
+    if (L->captured || !(L->pair || L->box) || !L->stream) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(L->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    L->captured = st != hipStreamCaptureStatusNone;
 }
 
 // Releases library-allocated adjoint buffers; caller workspace pointers are
@@ -1146,6 +1163,7 @@ lbm_status lbm_init_equilibrium(lbm_lattice* L, const float* rho, const float* u
     lbm_status st = usable(L);
     if (st != LBM_OK) return st;
     DeviceGuard guard(L->device);
+    note_capture(L);
     HIPCHK(L, lbmk::launch_init_eq(L->storage, L->d_f[L->cur], rho, u, L->dims, launch_of(L)));
     L->parity = 0;
     invalidate(L);
@@ -1189,6 +1207,7 @@ lbm_status lbm_macros(lbm_lattice* L, float* rho, float* u)
     if (st != LBM_OK) return st;
     if (!rho && !u) return fail(LBM_ERR_INVALID, "rho and u are both NULL");
     DeviceGuard guard(L->device);
+    note_capture(L);
     HIPCHK(L, lbmk::launch_macros(L->storage, L->parity, force_mode(L), L->d_f[L->cur], L->d_flags,
                                   L->d_force, rho, u, step_args(L), launch_of(L)));
     return LBM_OK;
@@ -1200,6 +1219,7 @@ lbm_status lbm_get_populations(lbm_lattice* L, float* f)
     if (st != LBM_OK) return st;
     if (!f) return fail(LBM_ERR_INVALID, "f is NULL");
     DeviceGuard guard(L->device);
+    note_capture(L);
     HIPCHK(L, lbmk::launch_get(L->storage, L->parity, L->d_f[L->cur], L->d_flags, f, L->dims, launch_of(L)));
     return LBM_OK;
 }
@@ -1210,6 +1230,7 @@ lbm_status lbm_set_populations(lbm_lattice* L, const float* f)
     if (st != LBM_OK) return st;
     if (!f) return fail(LBM_ERR_INVALID, "f is NULL");
     DeviceGuard guard(L->device);
+    note_capture(L);
     HIPCHK(L, lbmk::launch_set(L->storage, L->d_f[L->cur], f, L->dims, launch_of(L)));
     L->parity = 0;
     invalidate(L);
@@ -1290,6 +1311,7 @@ lbm_status lbm_forward_checkpointed(lbm_lattice* L, int T, int K)
         return fail(LBM_ERR_INVALID, "the trajectory buffer holds %zu bytes; T = %d, K = %d needs %zu", L->traj_bytes,
                     T, K, need);
     DeviceGuard guard(L->device);
+    note_capture(L);
     const int nck = T == 0 ? 1 : (T + K - 1) / K;
     st = hold_trajectory(L, nck, std::min(K, std::max(T, 1)) - 1);
     if (st != LBM_OK) return st;
@@ -1525,6 +1547,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
 lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, void* from, void* to)
 {
     if (n == 0) return LBM_OK;
+    note_capture(L);
     const StepLaunches sl = step_launches(L, from || to);
     const lbmk::StepArgs& args = sl.args;
     const int fm = collide ? force_mode(L) : lbmk::FORCE_NONE;
@@ -1537,13 +1560,12 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
     // arrays of the launch whose first step is s / whose last step is s
     auto in = [&](int s) { return s == 0 && from ? from : L->d_f[L->cur]; };
     auto out = [&](int s) { return s == n - 1 && to ? to : L->d_f[L->cur ^ 1]; };
-    // Two steps in one launch, and such launches in twos, so that the arrays
-    // are swapped as often as the steps would: a graph of an even number of
-    // steps, or of the fields, finds the state in the array that it was
-    // captured with. (Not with `to`: the state ends outside the two arrays.)
-    // Single steps where the last of the four is the one that stores rho and u
-    // or a finite check is due in between.
-    const int ci = L->check_interval, unit = to ? 2 : 4;
+    // Two steps in one launch; in a lattice that a graph holds calls on such
+    // launches come in twos, so that the arrays are swapped as often as the
+    // steps would. (Not with `to`: the state ends outside the two arrays.)
+    // Single steps where the last of them is the one that stores rho and u or a
+    // finite check is due in between.
+    const int ci = L->check_interval, unit = L->captured && !to ? 4 : 2;
     for (int s = 0; s < n; ++s) {
         if (pairs && n - s >= unit && !(rho && n - s == unit) && (ci == 0 || L->steps_done % ci + unit <= ci)) {
             for (const int end = s + unit; s < end; s += 2) {
