@@ -611,6 +611,7 @@ constexpr double POROUS_MIN_NEAR_FRACTION = 0.08;
 // Lattices without solid points up to this size step with one point per
 // work-item when the width is automatic.
 constexpr size_t SMALL_PERIODIC_MAX_POINTS = (size_t)1 << 18;
+bool small_periodic(const lbm_lattice* L) { return !L->walls && L->N <= SMALL_PERIODIC_MAX_POINTS; }
 
 // Whether the AB step of a lattice with automatic options takes one point per
 // work-item although its rows allow several. The one-point kernel has four or
@@ -638,7 +639,7 @@ bool one_point(const lbm_lattice* L, double near_fraction)
     const int nx = L->nx;
     const bool lines = (size_t)nx * storage_bytes(L->storage) % 64 == 0;
     const bool walls = near_fraction >= 0.01, porous = near_fraction >= POROUS_MIN_NEAR_FRACTION;
-    if (!L->walls && N <= SMALL_PERIODIC_MAX_POINTS) return true;
+    if (small_periodic(L)) return true;
     if (L->storage == LBM_STORAGE_F32)
         return L->onsite || (porous && lines) || (N <= 5000000 && (L->walls ? walls : lines || (L->dims.xcd && N > 300000)));
     if (nx >= 256 && N < (1u << 20)) return false;
@@ -896,7 +897,8 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     L->walls = (size_t)(unsigned)counts[2] != L->N;
     const bool automatic = L->pattern == LBM_PATTERN_AB && opt.cells_per_lane == 0 && opt.gather_mode == 0 &&
                            opt.groups_per_cu == 0 && opt.block_x == 0 && opt.block_y == 0;
-    if (L->cpl > 1 && automatic && one_point(L, near_fraction)) {
+    // (the small solid-free lattice also where only other options are given)
+    if (L->cpl > 1 && opt.cells_per_lane == 0 && (automatic ? one_point(L, near_fraction) : small_periodic(L))) {
         L->cpl = 1;
         L->flat = false;
     }

@@ -1,0 +1,40 @@
+"""The number of points per work-item where only other options are given: the
+options of the several-point step do not widen the step of a small lattice
+without solid points, which takes one point per work-item."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests.gpu_common import near_rest_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a ROCm device"
+    import paper_1309_1983_amd
+    paper_1309_1983_amd.lib()
+
+
+@pytest.mark.parametrize("kw", [{}, {"gather_mode": "early"}, {"gather_mode": "flags_first"}, {"groups_per_cu": -1},
+                                {"groups_per_cu": 4}, {"block": (32, 8)}])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+def test_small_solid_free_lattices_keep_one_point(kw, storage):
+    from paper_1309_1983_amd import Lattice
+    shape = (32, 32, 64)
+    N = int(np.prod(shape))
+    s0 = torch.from_numpy(near_rest_state(N, 5))
+    F = torch.from_numpy(W.random_force_field(N, 6, 1e-4).astype(np.float32))
+    out = []
+    for options in (kw, {"cells_per_lane": 4}):
+        lat = Lattice(*shape, 0.8, storage=storage, **options)
+        lat.set_force(F)
+        lat.set_populations(s0)
+        name = lat.step_kernel_name()
+        assert ("k_step_ab<" in name) == (options is kw), (options, name)
+        lat.step(4)
+        out.append(lat.populations())
+        lat.close()
+    assert torch.equal(*out)
