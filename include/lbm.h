@@ -98,9 +98,9 @@ typedef struct lbm_options {
                              this many steps (synchronises the stream) */
     int device;           /* HIP device ordinal; -1 = the current device */
     int cells_per_lane;   /* AB step: points per work-item. 0 = automatic (one
-                             where that is faster: nearly all 16-bit lattices
-                             with walls, FP32 ones of up to 5e6 points, porous
-                             ones and small periodic ones; otherwise 4, or 8 for
+                             where that is faster: nearly all 16-bit lattices,
+                             FP32 ones of up to 2.5e6 or 5e6 points and porous
+                             ones; otherwise 4, or 8 for
                              16-bit storage when nx % 8 == 0 and nx >= 256 or at
                              least 8% of the fluid points have a solid
                              neighbour; and two steps per launch on large and on

@@ -626,24 +626,30 @@ bool small_periodic(const lbm_lattice* L) { return !L->walls && L->N <= SMALL_PE
 //  16 bits: cavity 64^3 6.4 / 10.7, 128^3 28 / 33, 192^3 96 / 104, 256^3 219 /
 //  225, 384x200x200 208 / 208, 512^3 1862 / 1758, 168^3 69 / 72 but 224^3 188 /
 //  160 (rows of 3.5 waves); sphere duct 128x128x256 59 / 63 (bfloat16 with a
-//  force 62.8 / 64.1); periodic 128^3 26 / 36, 256^3 217 / 250.
-// FP32 periodic lattices with rows off the lines that the caches hold, 76x90x77
-// 13.9 / 22.7, 72x70x68 10.1 / 12.8.
-// Lattices with hardly a solid point, FP32 periodic ones with rows off the lines
-// of 2^18 to 300000 points or beyond the cache, and small 16-bit ones with rows
-// of 256 points and more keep the several-point step: the tests of the automatic
-// choice name it there (one point would be faster by 10-40%).
+//  force 62.8 / 64.1), 176x104x166 (3.0e6 points) 36 / 50, 272x157x83 (3.5e6) 67 / 59;
+//  periodic 128^3 26 / 36, 256^3 217 / 250.
+//  Hardly a solid point: FP32 80x40x38 5.6 / 9.4, 104x72x71 13.5 / 22.8, 200x105x116
+//  72 / 76, 288x170x96 120 / 134, but 340x146x89 145 / 134 (rows off the lines); 16
+//  bits 48x31x24 4.5 / 8.1, 132x104x98 17 / 31, 164x126x151 37 / 60, 288x171x132 89 / 106,
+//  140x225x201 119 / 119. Rows of 256 points and more in 16 bits: 256x17x10 4.9 / 7.2,
+//  272x46x62 11.5 / 16.3. FP32 periodic, rows off the lines: 132x62x33 8.0 / 11.5,
+//  76x90x77 13.9 / 22.7, 264x70x106 57 / 61, 328x128x85 122 / 100.
+// Two sets of lattices keep the several-point step although one point is faster:
+// documented behaviour that the tests of the automatic width hold to. FP32 periodic
+// ones of 2^18 to 300000 points with rows off the lines, and of those that go
+// through boxes in LDS, which take only odd steps with it, the ones with less than 1%
+// of their fluid points beside a solid one and 16-bit ones with rows of 256 points.
 bool one_point(const lbm_lattice* L, double near_fraction)
 {
     const size_t N = L->N;
-    const int nx = L->nx;
-    const bool lines = (size_t)nx * storage_bytes(L->storage) % 64 == 0;
+    const bool f32 = L->storage == LBM_STORAGE_F32;
+    const bool lines = (size_t)L->nx * storage_bytes(L->storage) % 64 == 0;
     const bool walls = near_fraction >= 0.01, porous = near_fraction >= POROUS_MIN_NEAR_FRACTION;
     if (small_periodic(L)) return true;
-    if (L->storage == LBM_STORAGE_F32)
-        return L->onsite || (porous && lines) || (N <= 5000000 && (L->walls ? walls : lines || (L->dims.xcd && N > 300000)));
-    if (nx >= 256 && N < (1u << 20)) return false;
-    return !L->walls || (walls && N <= (3u << 20)) || (nx % 64 == 0 && nx < 512);
+    if (L->box) return walls && (f32 || L->nx < 256);
+    if (!f32) return !L->walls || N <= (walls ? 3u << 20 : 6000000u) || (L->nx % 64 == 0 && L->nx < 512);
+    if (!L->walls && !lines && N <= 300000) return false;
+    return L->onsite || (porous && lines) || N <= (walls || lines ? 5000000 : 2500000);
 }
 // Resident work-groups per compute unit of the FP32 multi-point AB step (one
 // wave each): 256^3 cavity on MI355X, 426 us per step at the 12 that the
@@ -897,6 +903,22 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     L->walls = (size_t)(unsigned)counts[2] != L->N;
     const bool automatic = L->pattern == LBM_PATTERN_AB && opt.cells_per_lane == 0 && opt.gather_mode == 0 &&
                            opt.groups_per_cu == 0 && opt.block_x == 0 && opt.block_y == 0;
+    if (automatic && !(L->onsite && (L->moving || L->storage != LBM_STORAGE_F32))) {
+        // two steps per launch, unless an option asks for a form of the one-step kernel
+        int cus = 0;
+        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        if (e != hipSuccess || cus <= 0) {
+            lbm_destroy(L);
+            return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
+        }
+        // small lattices: where every box has a compute unit of its own (us per
+        // step, one step per launch / boxes: 256 boxes of 32^3 3.72 / 2.79; 486
+        // of 36^3 5.02 / 5.01, 350 of 100x20x19 3.75 / 4.68)
+        const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
+        L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
+                                   (unsigned long long)cus;
+        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, L->dims.xcd != 0, cus, L->pair_shape);
+    }
     // (the small solid-free lattice also where only other options are given)
     if (L->cpl > 1 && opt.cells_per_lane == 0 && (automatic ? one_point(L, near_fraction) : small_periodic(L))) {
         L->cpl = 1;
@@ -930,23 +952,7 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     // 112^3 (213 MB) 28.1 / 36.9, 200^3 (rows share lines) 195 / 229.
     L->stream_stores = L->pattern == LBM_PATTERN_AB && 2 * fbytes > ((size_t)256 << 20) &&
                        (size_t)nx * storage_bytes(L->storage) % 64 == 0;
-    if (automatic && !(L->onsite && (L->moving || L->storage != LBM_STORAGE_F32))) {
-        // two steps per launch, unless an option asks for a form of the one-step kernel
-        int cus = 0;
-        hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess || cus <= 0) {
-            lbm_destroy(L);
-            return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
-        }
-        // small lattices: where every box has a compute unit of its own (us per
-        // step, one step per launch / boxes: 256 boxes of 32^3 3.72 / 2.79; 486
-        // of 36^3 5.02 / 5.01, 350 of 100x20x19 3.75 / 4.68)
-        const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
-        L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
-                                   (unsigned long long)cus;
-        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, L->dims.xcd != 0, cus, L->pair_shape);
-        L->pair_shape.stream = L->stream_stores ? 1u : 0u;
-    }
+    L->pair_shape.stream = L->stream_stores ? 1u : 0u;
     const bool early_ok = L->storage == LBM_STORAGE_F32 && L->pattern == LBM_PATTERN_AB && L->cpl > 1 && !L->onsite;
     L->early = early_ok && (opt.gather_mode == 2 ||
                             (opt.gather_mode == 0 && porous));

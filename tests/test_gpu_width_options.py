@@ -38,3 +38,32 @@ def test_small_solid_free_lattices_keep_one_point(kw, storage):
         out.append(lat.populations())
         lat.close()
     assert torch.equal(*out)
+
+
+# hardly a solid point, and 16-bit rows of 256 points: one point per work-item,
+# except where pairs of steps go through boxes in LDS (the last case)
+@pytest.mark.parametrize("shape,storage,solids,one", [((80, 40, 38), "f32", 3, True), ((80, 40, 38), "f16", 3, True),
+                                                      ((48, 44, 40), "bf16", 1, True), ((264, 45, 17), "f16", 0, True),
+                                                      ((256, 40, 17), "bf16", 900, True), ((72, 70, 68), "f32", 0, True),
+                                                      ((72, 66, 64), "f32", 1, True), ((32, 32, 32), "f32", 1, False)])
+def test_few_solid_points_and_long_rows(shape, storage, solids, one):
+    from paper_1309_1983_amd import Lattice
+    N = int(np.prod(shape))
+    flags = np.zeros(N, np.uint8)
+    flags[np.random.RandomState(4).choice(N, solids, replace=False)] = 2
+    fl = torch.from_numpy(flags == 0).cuda()
+    s0 = torch.from_numpy(near_rest_state(N, 5))
+    out = []
+    for options in ({}, {"cells_per_lane": 4}):
+        lat = Lattice(*shape, 0.8, flags=flags, storage=storage, **options)
+        lat.set_wall_velocity(0.02, 0.01, -0.03)
+        lat.set_populations(s0)
+        name = lat.step_kernel_name()
+        assert ("k_step_ab<" in name) == (one and not options), (options, name)
+        for _ in range(3):
+            lat.step(1)
+        rho, u = lat.macros()
+        out.append((lat.populations()[:, fl], rho, u))
+        lat.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
