@@ -677,12 +677,15 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 // with walls it only drew level (256^3 FP16 cavity 436 / 446 us) or lost
 // (sphere duct 150 / 134).
 //
-// On-site walls cost a plane 8.4 us and more (the rebuild runs in every wave
-// that holds a box side), and no less where the arrays fit the cache; their
-// single step reaches 5.8 TB/s, off the lines 5.1 or 4.7. us per step, single /
-// pair: 132x131x131 77.7 / 67.8, 256^3 432 / 361, 182x193x490 656 / 537; but
-// 128^3 56.2 / 58.2, 160^3 107 / 124, 140x110x150 76 / 86, 139x131x131 (363 MB) 89 / 97,
-// 130x128x107 (271 MB) 48 / 52, 112^3 (213 MB) 39 / 46.
+// On-site walls cost a plane 8.4 us, off the lines 9.6, whatever the tile (the
+// rebuild runs in every wave that holds a box side and bounds it: 704 to 1024
+// work-items 8.0 to 8.7 and 8.9 to 10.5 us), and no less where the arrays fit the
+// cache; their single step reaches 5.6 TB/s, off the lines 5.15 with planes on 64
+// bytes, 4.7 with rows on 16 bytes, else 4.2. us per step, single / pair: 132x131x131 72.7 / 69.7, 223x120x100 94.7 / 92.6, 192x128x100 71.6 / 67.2,
+// 150^3 117 / 105, 256^3 431 / 361; but 144x120x130 62.6 / 78.1, 144^3 84 / 96,
+// 140x110x150 72.9 / 87.6, 139x131x131 83 / 95, 160^3 107 / 124, 112^3 35 / 45. Over
+// 82 shapes of 1.3e6 to 2e7 points the choice costs 0.4% on average, at most
+// 7% (196x110x120).
 //
 // Where the one-point kernel gives each XCD an eighth of the lattice (xcd) it
 // reaches 7.2 TB/s from the caches (6.4 on rows off 16 bytes), us per step, pair
@@ -703,7 +706,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     // a single step: bytes at the rate its kernel reaches, plus its launch
     const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
     const bool lines = (size_t)nx * (f32 ? 4 : 2) % 64 == 0;   // rows start on 64-byte lines
-    const double rate = xcd ? (nx % 4 == 0 ? 7.2e6 : 6.4e6) : onsite ? (lines ? 5.8e6 : ((size_t)nx * ny % 16 == 0 ? 5.1e6 : 4.7e6))
+    const double rate = xcd ? (nx % 4 == 0 ? 7.2e6 : 6.4e6) : onsite ? (lines ? 5.6e6 : (size_t)nx * ny % 16 == 0 ? 5.15e6 : nx % 4 == 0 ? 4.7e6 : 4.2e6)
                                : f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
     const double single = bytes / rate + 2.5;
     lbmk::PairShape ps{};
@@ -718,11 +721,11 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
-    if (onsite && bytes < (nx % 4 == 0 ? 320e6 : 400e6)) return false;   // largely held by the cache
-    const double full = onsite ? 8.4 : f32 ? (walls ? 6.6 : 6.1) : 4.4;
+    const double full = f32 ? (walls ? 6.6 : 6.1) : 4.4;
     const double fill = ps.threads / 1024.0;
     // from the cache a plane costs less, and not in proportion to its work-items
-    const double plane = cached ? (walls ? 3.5 + 1.4 * fill : 1.6 + 2.45 * fill)
+    const double plane = onsite ? (lines ? 8.4 : 9.6)
+                       : cached ? (walls ? 3.5 + 1.4 * fill : 1.6 + 2.45 * fill)
                                 : full * (lines ? 1.0 : 1.2) * std::max(0.5, fill);
     // a few columns short of whole 64-byte lines: take them (us per step, before
     // / after: 140x110x150 cavity 47 columns 69.9 / 65.6, 292x192x401 59

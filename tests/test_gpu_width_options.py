@@ -67,3 +67,22 @@ def test_few_solid_points_and_long_rows(shape, storage, solids, one):
         lat.close()
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# two steps per launch beside on-site walls: the cost of a plane does not fall
+# with the width of the tile (48 columns in the second and third)
+@pytest.mark.parametrize("shape,pair", [((192, 128, 100), True), ((144, 120, 130), False), ((144, 144, 144), False),
+                                        ((112, 112, 112), False)])
+def test_pairs_beside_onsite_walls(shape, pair):
+    from paper_1309_1983_amd import Lattice
+    flags = W.onsite_cavity_flags(*shape)
+    fl = torch.from_numpy((flags != 1) & (flags != 2)).cuda()
+    out = []
+    for options in ({}, {"cells_per_lane": 1}):
+        lat = Lattice(*shape, 0.8, flags=flags, **options)
+        lat.set_wall_velocity(0.02, 0.01, 0.0)
+        assert ("k_step_pair<" in lat.step_kernel_name()) == (pair and not options)
+        lat.step(5)
+        out.append(lat.populations()[:, fl])
+        lat.close()
+    assert torch.equal(*out)
