@@ -10,6 +10,7 @@
 // d3q19.hpp): the structure-of-arrays coalescing of Section 4.1, with the 19
 // planes of a slab next to each other so that the concurrently running
 // work-groups stream through a compact address window.
+#include <algorithm>
 #include <type_traits>
 
 #include "step_common.hpp"
@@ -671,10 +672,18 @@ hipError_t resolve_step_kernel(bool vector, int storage, int pattern, int parity
 
 hipError_t launch_copy(const float* src, float* dst, size_t n, hipStream_t s)
 {
-    if (n == 0) return hipSuccess;
-    const size_t blocks = (n / 4 + 1 + 255) / 256;   // whole chunks plus the tail work-item
-    hipLaunchKernelGGL(k_copy, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, n);
-    return hipGetLastError();
+    // a launch may have less than 2^32 work-items of four floats each: one FP32
+    // state has more from 9.04e8 points on
+    constexpr size_t most = (size_t)1 << 33;
+    for (; n > 0; src += most, dst += most) {
+        const size_t part = std::min(n, most);
+        const size_t blocks = (part / 4 + 1 + 255) / 256;   // whole chunks plus the tail work-item
+        hipLaunchKernelGGL(k_copy, dim3((unsigned)blocks), dim3(256), 0, s, src, dst, part);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        n -= part;
+    }
+    return hipSuccess;
 }
 
 }  // namespace lbmk
