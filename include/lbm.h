@@ -186,7 +186,7 @@ lbm_status lbm_query_buffer_sizes(int nx, int ny, int nz, const lbm_options* opt
 
 /* Bytes of the checkpoint store lbm_forward_checkpointed(T, K) uses on a
  * lattice of nx*ny*nz points: ceil(T/K) checkpoints plus min(K, T) - 1
- * recomputed states (at least one checkpoint), each state_bytes. 0 for
+ * states inside a segment (at least one checkpoint), each state_bytes. 0 for
  * invalid arguments. */
 size_t lbm_trajectory_bytes(int nx, int ny, int nz, int T, int K);
 
@@ -195,7 +195,9 @@ size_t lbm_trajectory_bytes(int nx, int ny, int nz, int T, int K);
  * whose lbm_trajectory_bytes exceeds `bytes` fail with LBM_ERR_INVALID instead
  * of allocating. NULL returns to library-allocated storage. Drops a recorded
  * trajectory. The buffer must stay alive and untouched by the caller until
- * it is replaced or the lattice is destroyed. */
+ * it is replaced or the lattice is destroyed: all of it carries states from
+ * lbm_forward_checkpointed to lbm_adjoint, the part beyond the checkpoints
+ * (min(K, T) - 1 states) those inside the last segment. */
 lbm_status lbm_set_trajectory_buffer(lbm_lattice* lat, void* dev, size_t bytes);
 
 /* Gives the lattice a caller-owned device workspace for lbm_adjoint of at
@@ -308,8 +310,10 @@ lbm_status lbm_forward_checkpointed(lbm_lattice* lat, int T, int K);
  * dL_du_dev: [3][N] gradient of a scalar loss with respect to u(T) as
  * returned by lbm_macros (values at solid points are ignored). Writes
  * grad_F_dev [3][N] = dL/dF (overwritten; zero at solid points) and
- * *grad_tau_host = dL/dtau. Recomputes each segment from its checkpoint,
- * then runs the reverse step for every time step of the segment.
+ * *grad_tau_host = dL/dtau. Recomputes each segment's states from its
+ * checkpoint, except the last one's, which the rollout left in the store (a
+ * second call on the same trajectory recomputes them too), then runs the
+ * reverse step for every time step of the segment.
  * Synchronises the stream before returning (grad_tau is a host value).
  * Errors: LBM_ERR_STATE without a valid trajectory (parameters, state or
  * force changed since it was recorded); LBM_ERR_INVALID; LBM_ERR_OOM.

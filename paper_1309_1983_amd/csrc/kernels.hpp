@@ -164,9 +164,9 @@ hipError_t launch_adjoint_step(bool direct, int force_mode, const float* s, cons
                                const uint32_t* smask, const uint32_t* mmask, const float* ffield,
                                const StepArgs& args, float inv_tau2, const Launch& L);
 
-// The same reverse step with vw = 2 consecutive x-points per work-item
-// (nx % vw == 0, at most 256 work-items per group, grid counting groups).
-hipError_t launch_adjoint_stepv(int vw, bool direct, int force_mode, const float* s, const float* bin,
+// The same reverse step with two consecutive x-points per work-item
+// (nx even, at most 256 work-items per group, grid counting groups).
+hipError_t launch_adjoint_stepv(bool direct, int force_mode, const float* s, const float* bin,
                                 float* bout, float* gF, double* taupart, const uint8_t* flags,
                                 const uint32_t* smask, const uint32_t* mmask, const float* ffield,
                                 const StepArgs& args, float inv_tau2, const Launch& L);

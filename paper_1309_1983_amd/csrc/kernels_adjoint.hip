@@ -257,23 +257,9 @@ __global__ __launch_bounds__(256) void k_adj_step(const float* __restrict__ s,
     block_tau_sum((double)tterm, taupart);
 }
 
-// Flag bytes of VW consecutive points as one word.
-template <int VW>
-struct FlagBytes;
-template <>
-struct FlagBytes<2> {
-    typedef uint16_t t;
-    static constexpr uint16_t ones = 0x0101u;
-};
-template <>
-struct FlagBytes<4> {
-    typedef uint32_t t;
-    static constexpr uint32_t ones = 0x01010101u;
-};
-
-// Reverse step with VW consecutive x-points per work-item (nx % VW == 0):
+// Reverse step with two consecutive x-points per work-item (nx even):
 // the state is gathered from x - e_i and the adjoint from x + e_i with the
-// 16-byte shifted accesses of the forward vector kernel (gather_vec); each
+// shifted accesses of the forward vector kernel (gather_vec); each
 // point then runs the same adj_cell arithmetic as the one-point kernel, so
 // b and dL/dF agree with it bit for bit. The launch bound asks for three
 // waves per SIMD (168 VGPRs for two points per work-item): against two waves
@@ -282,7 +268,7 @@ struct FlagBytes<4> {
 // point inside the cell loop and dL/dF is read after it, so neither is held
 // across the loop: with a force field this removed 20 bytes of scratch per
 // work-item (reverse-step counter traffic was 1.11x its 264 bytes per point).
-template <int FM, bool DIRECT, int VW>
+template <int FM, bool DIRECT>
 __global__ __launch_bounds__(256, 3) void k_adj_stepv(const float* __restrict__ s,
                                                    const float* __restrict__ bin,
                                                    float* __restrict__ bout, float* __restrict__ gF,
@@ -293,10 +279,11 @@ __global__ __launch_bounds__(256, 3) void k_adj_stepv(const float* __restrict__ 
                                                    const float* __restrict__ ff, StepArgs a,
                                                    float inv_tau2)
 {
+    constexpr int VW = 2;
     using Vt = typename Vec<float, VW>::t;
-    using FW = typename FlagBytes<VW>::t;
+    using FW = uint16_t;   // the flag bytes of the two points
     constexpr bool FORCE = FM != FORCE_NONE;
-    constexpr FW ONES = FlagBytes<VW>::ones;
+    constexpr FW ONES = 0x0101u;
     const Dims& d = a.d;
     // agx > 0: rows whose group count does not divide into waves run on a
     // one-dimensional grid over the plane (agx groups per row)
@@ -444,37 +431,28 @@ static hipError_t adj_fm(bool direct, const float* s, const float* bin, float* b
     return hipGetLastError();
 }
 
-template <int FM, int VW>
+template <int FM>
 static hipError_t adjv_fm(bool direct, const float* s, const float* bin, float* bout, float* gF,
                           double* tp, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
                           const float* ff, const StepArgs& a, float it2, const Launch& L)
 {
     if (direct)
-        hipLaunchKernelGGL((k_adj_stepv<FM, true, VW>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_stepv<FM, true>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
     else
-        hipLaunchKernelGGL((k_adj_stepv<FM, false, VW>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
+        hipLaunchKernelGGL((k_adj_stepv<FM, false>), L.grid, L.block, L.shmem, L.stream, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2);
     return hipGetLastError();
 }
 
-template <int VW>
-static hipError_t adjv_vw(bool direct, int fm, const float* s, const float* bin, float* bout, float* gF,
-                          double* tp, const uint8_t* flags, const uint32_t* sm, const uint32_t* mm,
-                          const float* ff, const StepArgs& a, float it2, const Launch& L)
-{
-    switch (fm) {
-    case FORCE_UNIFORM: return adjv_fm<FORCE_UNIFORM, VW>(direct, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2, L);
-    case FORCE_FIELD: return adjv_fm<FORCE_FIELD, VW>(direct, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2, L);
-    default: return adjv_fm<FORCE_NONE, VW>(direct, s, bin, bout, gF, tp, flags, sm, mm, ff, a, it2, L);
-    }
-}
-
-hipError_t launch_adjoint_stepv(int vw, bool direct, int fm, const float* s, const float* bin, float* bout,
+hipError_t launch_adjoint_stepv(bool direct, int fm, const float* s, const float* bin, float* bout,
                                 float* gF, double* taupart, const uint8_t* flags, const uint32_t* smask,
                                 const uint32_t* mmask, const float* ff, const StepArgs& args,
                                 float inv_tau2, const Launch& L)
 {
-    if (vw == 2) return adjv_vw<2>(direct, fm, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
-    return hipErrorInvalidValue;
+    switch (fm) {
+    case FORCE_UNIFORM: return adjv_fm<FORCE_UNIFORM>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
+    case FORCE_FIELD: return adjv_fm<FORCE_FIELD>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
+    default: return adjv_fm<FORCE_NONE>(direct, s, bin, bout, gF, taupart, flags, smask, mmask, ff, args, inv_tau2, L);
+    }
 }
 
 template <bool STREAM>

@@ -1538,7 +1538,7 @@ lbm_status adjoint_sweep(lbm_lattice* L, const float* g, float* gF, float* adj[2
         L->seg_of = k;
         for (int j = len - 1; j >= 0; --j) {
             if (vec)
-                HIPCHK(L, lbmk::launch_adjoint_stepv(2, direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part,
+                HIPCHK(L, lbmk::launch_adjoint_stepv(direct, fm, state(j), adj[ab], adj[ab ^ 1], gF, part,
                                                      L->d_flags, L->d_smask, L->d_mmask, L->d_force, rargs, inv_tau2,
                                                      LR));
             else
