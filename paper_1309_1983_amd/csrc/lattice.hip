@@ -542,11 +542,16 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     if (opt.groups_per_cu < -1 || opt.groups_per_cu > 64)
         return fail(LBM_ERR_INVALID, "groups_per_cu must be -1, 0 or 1..64 (got %d)", opt.groups_per_cu);
     int bx = opt.block_x, by = opt.block_y;
-    // Rows that do not fill waves: a one-dimensional grid, or, between two
-    // arrays, one row per work-group where rows are long and the last wave is
-    // not mostly idle (MI355X, 260x259x259 FP32 574 / 559 us; in place 280 / 296)
+    // Rows that do not fill waves: a one-dimensional grid, whose waves store whole
+    // lines where planes begin on them, or one row per work-group where neither
+    // form stores whole lines and the row leaves hardly a lane idle. MI355X, us per
+    // step, a row per work-group / one-dimensional: FP32 cavity 257x256x256 655 / 451,
+    // 380x200x100 263 / 200, 321x300x300 1017 / 898, 511x300x200 1055 / 982 (but
+    // 260x259x259 567 / 585); 16-bit spheres 257x256x256 330 / 238, 444x180x150 229 /
+    // 218, but 383x250x250 441 / 470, 510x150x100 143 / 151, 511x300x200 580 / 606.
     const int row = (nx + 63) / 64 * 64;
-    const bool rows = opt.pattern == LBM_PATTERN_AB && nx >= 192 && row <= 1024 && 4 * row <= 5 * nx;
+    const bool rows = opt.pattern == LBM_PATTERN_AB && storage_bytes(opt.storage) == 2 && nx >= 256 && row <= 1024 &&
+                      row - nx <= 4 && (size_t)nx * (size_t)ny % 32 != 0;
     const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows;
     if (flat1) { bx = 256; by = 1; }
     else if (bx == 0 && by == 0 && !wave_rows(nx)) { bx = row; by = 1; }
