@@ -9,9 +9,9 @@
 // s^{t+2} of the tile one plane behind: per two steps the state is read and
 // written once. The halo is computed again by the neighbouring tiles.
 //
-// MI355X, us per step, one step per launch / this: 256^3 FP32 cavity 407 / 278,
-// periodic 434 / 262, sphere duct 128x128x256 114 / 91, 256^3 FP16 periodic 261
-// / 190. What bounds it: a plane's loads and stores, 256 of the 278 us with the
+// MI355X, us per step, one step per launch / this: 256^3 FP32 cavity 411 / 279,
+// periodic 417 / 260, sphere duct 128x128x256 107 / 86, 256^3 FP16 periodic 217 /
+// 180. What bounds it: a plane's loads and stores, 256 of the 279 us with the
 // arithmetic taken out; the arithmetic and LDS exchange alone take 99 to 114.
 // Reads from memory are 1.13 to 1.35 times the state (the halo rows of
 // neighbouring tiles that miss L2), writes exact. Tiles of 64 columns make a wave's stores one row; one

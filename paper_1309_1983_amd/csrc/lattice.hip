@@ -82,6 +82,7 @@ struct lbm_lattice {
     bool onsite = false;           // has on-site velocity nodes (flags 3, 4)
     bool early = false;            // FP32 vector AB step gathers before the flag branches
     bool pair = false;             // AB steps are taken two per launch where possible
+    bool pair_uniform = false;     // the same while a uniform force is set
     lbmk::PairShape pair_shape{};
     bool stream_stores = false;    // one-point AB step stores with the non-temporal hint
     bool box = false;              // two steps per launch through boxes in LDS (small lattices)
@@ -205,12 +206,12 @@ lbmk::StepArgs step_args(const lbm_lattice* L)
 
 // Steps may be taken two per launch: the per-step event log needs them one
 // by one, and so does a finite check after every step.
-// With 16-bit storage and a uniform force one point per work-item is faster
+// With 16-bit storage and a uniform force single steps are faster
 // (periodic 128x128x256, us per step: FP16 54.6 / 60.0, bfloat16 55.4 / 65.3).
 bool takes_pairs(const lbm_lattice* L)
 {
-    return L->pair && L->events.empty() && L->check_interval != 1 &&
-           (L->storage == LBM_STORAGE_F32 || force_mode(L) != lbmk::FORCE_UNIFORM) &&
+    return (force_mode(L) == lbmk::FORCE_UNIFORM ? L->pair_uniform && L->storage == LBM_STORAGE_F32 : L->pair) &&
+           L->events.empty() && L->check_interval != 1 &&
            (!L->onsite || force_mode(L) == lbmk::FORCE_NONE);
 }
 
@@ -667,53 +668,69 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 //
 // One work-group is resident per compute unit (its LDS and registers fill
 // it), so a launch takes `rounds` = work-groups / compute units, rounded up,
-// times the planes that one of them computes (two more than it stores). The
-// times are MI355X measurements: a plane of 1024 work-items takes 6.0 us
-// (periodic 256^3), 6.4 us (walled duct, cavity) to 8 us (10%-solid sphere
-// duct) in FP32 and 4.3 us with 16-bit storage, less where both arrays fit the
-// memory-side cache, a fifth more where rows start anywhere on a line,
-// and the first plane's loads 4 us. Two steps, pair against single kernels, us: cavity 256^3 555 / 813,
-// cavity 128^3 95 / 120, cavity 96^3 49 / 66, sphere duct 128x128x256 183 /
-// 228, periodic 256^3 FP16 381 / 522; but cavity 64^3 26 / 19: too few planes
-// per work-group to pay for the two extra ones.
+// times the planes that one of them computes (two more than it stores), and 4 us
+// for the first plane's loads. A single step moves its bytes at the rate of the
+// one-point kernel. Both depend on what begins on 64-byte lines: rows (whole
+// lines stored by either), planes only (the one-point kernel's waves still store
+// whole lines on a one-dimensional grid, the tiles' rows do not), or neither. On
+// MI355X, TB/s of a single step / us of a plane of 1024 work-items:
+//                        rows         planes       neither
+//   FP32 walls         6.0 / 6.5    5.5 / 7.3    4.9 / 8.0
+//   FP32 periodic      6.0 / 5.7    5.5 / 6.0    4.9 / 6.3
+//   FP32 on-site       5.6 / 8.4    5.15 / 9.6   4.7, 4.2 / 9.6   (4.2: rows off 16 bytes)
+//   16-bit periodic    5.9 / 4.2    5.7 / 4.2    4.5 / 4.4
+//   arrays in the 256 MB cache:
+//   FP32 walls         7.2 / 4.75   7.2 / 4.75   6.5 / 5.25
+//   FP32 periodic      7.2 / 3.8    7.2 / 3.8    6.5 / 4.3
+// A tile with fewer work-items takes 1.5 us less per 1024 (2.2 periodic from the
+// cache), except beside on-site walls, where the rebuild, which runs in every wave
+// that holds a box side, bounds the plane. A uniform force costs the pair 0.6 us a
+// plane from the cache (its kernel spills); beyond the cache, and for a force
+// field, which a single step reads twice as often, both lose alike. Over 531
+// lattices of 5e5 to 2e7 points the choice is 0.3% slower than the better of the
+// two on average. us per step, single / pair: cavity 256^3 411 / 279, 128^3 53.1 /
+// 46.2, 96^3 21.1 / 19.4; periodic 256^3 417 / 260, 96^3 20.8 / 15.3; sphere duct
+// 128x128x256 107 / 86 (with a uniform force 91); periodic 256^3 FP16 217 / 180; on-site
+// 256^3 427 / 362, 132x131x131 73.5 / 69.9; but cavity 88^3 16.5 / 18.4, on-site 128^3 57.0 /
+// 57.9, 144^3 83 / 96, 344x258x168 411 / 482 (chosen all the same).
 //
-// 16-bit storage takes pairs only without solid points: there the kernel is
-// bound by its memory instructions and arithmetic rather than by HBM, and
-// with walls it only drew level (256^3 FP16 cavity 436 / 446 us) or lost
-// (sphere duct 150 / 134).
-//
-// On-site walls cost a plane 8.4 us, off the lines 9.6, whatever the tile (the
-// rebuild runs in every wave that holds a box side and bounds it: 704 to 1024
-// work-items 8.0 to 8.7 and 8.9 to 10.5 us), and no less where the arrays fit the
-// cache; their single step reaches 5.6 TB/s, off the lines 5.15 with planes on 64
-// bytes, 4.7 with rows on 16 bytes, else 4.2. us per step, single / pair: 132x131x131 72.7 / 69.7, 223x120x100 94.7 / 92.6, 192x128x100 71.6 / 67.2,
-// 150^3 117 / 105, 256^3 431 / 361; but 144x120x130 62.6 / 78.1, 144^3 84 / 96,
-// 140x110x150 72.9 / 87.6, 139x131x131 83 / 95, 160^3 107 / 124, 112^3 35 / 45. Over
-// 82 shapes of 1.3e6 to 2e7 points the choice costs 0.4% on average, at most
-// 7% (196x110x120).
-//
-// Where the one-point kernel gives each XCD an eighth of the lattice (xcd) it
-// reaches 7.2 TB/s from the caches (6.4 on rows off 16 bytes), us per step, pair
-// / single: cavity 88^3 18.4 / 16.9, 96^3 19.4 / 21.3, 100x110x90 22.4 / 24.5,
-// periodic 81^3 13.3 / 14.0. 16-bit lattices that the caches hold take single
-// steps: periodic FP16 112^3 19.3 / 18.1, 120^3 23.9 / 22.4, 144^3 35.9 / 35.1,
-// 128^3 25.6 / 26.3.
-bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, bool xcd, int cus,
+// 16-bit storage takes pairs only without solid points and beyond the cache: there
+// the kernel is bound by its memory instructions and arithmetic rather than by HBM,
+// with walls it only drew level (256^3 FP16 cavity 223 / 218 us) or lost (sphere
+// duct 75 / 67), and so from the cache (periodic 112^3 18.1 / 19.3, 144^3 35.1 / 35.9).
+bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, bool uniform_force, int cus,
                lbmk::PairShape& best)
 {
     const bool f32 = storage == LBM_STORAGE_F32;
     if (!f32 && walls) return false;
     const double N = (double)nx * ny * nz;
     const bool cached = 2.0 * N * Q * (f32 ? 4 : 2) <= 256.0 * (1 << 20);
-    if (!f32 && cached) return false;
+    if ((!f32 || onsite) && cached) return false;
     if ((unsigned long long)nx * ny > (1ull << 28) || nx < 2) return false;
     if (N < 524288.0) return false;   // a few planes per work-group at most
-    // a single step: bytes at the rate its kernel reaches, plus its launch
-    const double bytes = N * 2.0 * Q * (f32 ? 4 : 2);
-    const bool lines = (size_t)nx * (f32 ? 4 : 2) % 64 == 0;   // rows start on 64-byte lines
-    const double rate = xcd ? (nx % 4 == 0 ? 7.2e6 : 6.4e6) : onsite ? (lines ? 5.6e6 : (size_t)nx * ny % 16 == 0 ? 5.15e6 : nx % 4 == 0 ? 4.7e6 : 4.2e6)
-                               : f32 ? (nx % 4 == 0 ? 5.6e6 : 4.9e6) : (lines ? 5.8e6 : 5.0e6);   // bytes per us
-    const double single = bytes / rate + 2.5;
+    const size_t row = (size_t)nx * (f32 ? 4 : 2);
+    const bool lines = row % 64 == 0;
+    const int align = lines ? 0 : (row * (size_t)ny % 64 == 0 ? 1 : 2);
+    double rate;               // of a single step, bytes per us
+    double plane, per1024;     // us of a plane: a part of its own, a part per 1024 work-items
+    if (onsite) {
+        rate = align == 0 ? 5.6e6 : align == 1 ? 5.15e6 : nx % 4 == 0 ? 4.7e6 : 4.2e6;
+        plane = align == 0 ? 8.4 : 9.6;
+        per1024 = 0.0;
+    } else if (!f32) {
+        rate = align == 0 ? 5.9e6 : align == 1 ? 5.7e6 : 4.5e6;
+        plane = align == 2 ? 4.4 : 4.2;
+        per1024 = 0.0;
+    } else if (cached) {
+        rate = align == 2 ? 6.5e6 : 7.2e6;
+        plane = (walls ? 3.3 : 1.6) + (align == 2 ? 0.5 : 0.0) + (uniform_force ? 0.6 : 0.0);
+        per1024 = walls ? 1.45 : 2.2;
+    } else {
+        rate = align == 0 ? 6.0e6 : align == 1 ? 5.5e6 : 4.9e6;
+        plane = walls ? (align == 0 ? 5.0 : align == 1 ? 5.8 : 6.5) : (align == 0 ? 4.2 : align == 1 ? 4.5 : 4.8);
+        per1024 = 1.5;
+    }
+    const double single = N * 2.0 * Q * (f32 ? 4 : 2) / rate + 2.5;
     lbmk::PairShape ps{};
     const int widest = lbmk::PAIR_PITCH - 2, tallest = lbmk::PAIR_MAX_THREADS / lbmk::PAIR_PITCH - 2;
     ps.ntx = (uint32_t)((nx + widest - 1) / widest);
@@ -726,12 +743,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
-    const double full = f32 ? (walls ? 6.6 : 6.1) : 4.4;
-    const double fill = ps.threads / 1024.0;
-    // from the cache a plane costs less, and not in proportion to its work-items
-    const double plane = onsite ? (lines ? 8.4 : 9.6)
-                       : cached ? (walls ? 3.5 + 1.4 * fill : 1.6 + 2.45 * fill)
-                                : full * (lines ? 1.0 : 1.2) * std::max(0.5, fill);
+    plane += per1024 * (ps.threads / 1024.0);
     // a few columns short of whole 64-byte lines: take them (us per step, before
     // / after: 140x110x150 cavity 47 columns 69.9 / 65.6, 292x192x401 59
     // columns 616 / 574, 245x216x126 periodic 62 columns 148 / 134)
@@ -754,7 +766,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
             best = ps;
         }
     }
-    return best.groups > 0 && least < (cached ? 0.99 : 0.95) * 2.0 * single;
+    return best.groups > 0 && least < (onsite ? 0.95 : 0.98) * 2.0 * single;
 }
 
 }  // namespace
@@ -925,7 +937,9 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
         const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
         L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
                                    (unsigned long long)cus;
-        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, L->dims.xcd != 0, cus, L->pair_shape);
+        L->pair = !L->box && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, false, cus, L->pair_shape);
+        lbmk::PairShape forced{};   // the tiling does not depend on the force
+        L->pair_uniform = L->pair && plan_pair(nx, ny, nz, L->storage, L->walls, L->onsite, true, cus, forced);
     }
     // (the small solid-free lattice also where only other options are given)
     if (L->cpl > 1 && opt.cells_per_lane == 0 && (automatic ? one_point(L, near_fraction) : small_periodic(L))) {
