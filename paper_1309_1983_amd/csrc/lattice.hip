@@ -867,6 +867,12 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
     if (!L) return fail(LBM_ERR_OOM, "host allocation failed");
     L->nx = nx; L->ny = ny; L->nz = nz; L->N = (size_t)N;
     L->dims = dims_of(nx, ny, nz);
+    // Small lattices with on-site nodes: nearly every wave runs the rebuild, whose
+    // arithmetic (1.3 us) the launch pays once for each such wave on a SIMD. Groups
+    // of one wave spread over the chip, groups of four sometimes share a compute
+    // unit. MI355X, us per step in place, groups of 256 / 64: 48x19x21 6.5 / 5.4,
+    // 20x28x19 6.9 / 5.1, 57x33x44 5.95 / 5.84, 39x63x68 (1.7e5 points) 7.3 / 7.4.
+    if (onsite && lay.flat1 && N <= (1u << 17)) lay.bx = 64;
     L->dims.flat = lay.flat1 ? 1u : 0u;
     L->device = dev;
     L->storage = opt.storage;
