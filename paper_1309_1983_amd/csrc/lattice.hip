@@ -582,16 +582,17 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
             // take a one-dimensional grid over the plane instead, unless one wave
             // per row leaves few lanes idle and the other form's waves begin
             // anywhere: FP32 rows on 64-byte lines in planes that are no multiple of
-            // a wave's 1 KB, and 16-bit planes off the lines. MI355X, us per step,
+            // a wave's 1 KB, and 16-bit planes off the lines or rows on them. MI355X, us per step,
             // one- / two-dimensional: FP32 storing rho and u, 160x253x164 (40 groups) 210 /
             // 203, 176x222x174 cavity 1.05 times as fast, 144x218x123 (36 groups) 0.95
             // times, but 192^3 201 / 207, 160x192x256 225 / 234; 16 bits 228x143x422 (57
-            // groups) cavity 284 / 274, 204x293x289 (51) 0.96 to 1.01 times; with planes
+            // groups) cavity 284 / 274, 216x195x191 (54) 131 / 127, 224x139x406 (56) duct with
+            // a force 184 / 175, but 204x293x289 (51) 0.96 to 1.01 times; with planes alone
             // on the lines, 240x200x149 (60) 0.91 to 0.96 times, 236x200x300 275 / 326.
             const int groups = nx / vw;
             const size_t es = storage_bytes(opt.storage), plane_bytes = (size_t)nx * (size_t)ny * es;
             const bool one_wave = groups <= 64 && (es == 4 ? nx % 16 == 0 && plane_bytes % 1024 != 0 && 5 * groups >= 3 * 64
-                                                           : plane_bytes % 64 != 0 && 20 * groups >= 17 * 64);
+                                                           : (plane_bytes % 64 != 0 || nx % 32 == 0) && groups >= 52);
             bx4 = std::min(groups, 64);
             by4 = std::max(1, 64 / bx4);
             flat = !wave_rows(groups) && !one_wave;
