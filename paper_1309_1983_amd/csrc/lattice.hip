@@ -553,9 +553,17 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     const int row = (nx + 63) / 64 * 64;
     const bool rows = opt.pattern == LBM_PATTERN_AB && storage_bytes(opt.storage) == 2 && nx >= 256 && row <= 1024 &&
                       row - nx <= 4 && (size_t)nx * (size_t)ny % 32 != 0;
-    const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows;
+    // Between two arrays that the cache does not hold, with planes off the lines,
+    // rows of 105 to 127 points stay on the two-dimensional grid, two to a group.
+    // Speed against the one-dimensional grid: cavity 126x225x247 1.17 in bfloat16,
+    // 1.10 in FP32, on-site walls 1.14, periodic 1.0; 118x109x364 1.14, 1.06, 1.10, 1.0;
+    // but 141x169x464 0.95, and in place 0.97 to 1.02.
+    const size_t es = storage_bytes(opt.storage);
+    const bool two_rows = opt.pattern == LBM_PATTERN_AB && nx >= 105 && nx < 128 && (size_t)nx * (size_t)ny * es % 64 != 0 &&
+                          2 * (size_t)Q * (size_t)N * es > ((size_t)256 << 20);
+    const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows && !two_rows;
     if (flat1) { bx = 256; by = 1; }
-    else if (bx == 0 && by == 0 && !wave_rows(nx)) { bx = row; by = 1; }
+    else if (bx == 0 && by == 0 && rows) { bx = row; by = 1; }
     if (bx == 0 && by == 0) default_block(nx, bx, by);
     if (bx <= 0 || by <= 0 || bx * by > 1024) return fail(LBM_ERR_INVALID, "bad block shape %dx%d", bx, by);
     // ny has the limit of the two-dimensional grid also on the one-dimensional one
@@ -590,7 +598,7 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
             // a force 184 / 175, but 204x293x289 (51) 0.96 to 1.01 times; with planes alone
             // on the lines, 240x200x149 (60) 0.91 to 0.96 times, 236x200x300 275 / 326.
             const int groups = nx / vw;
-            const size_t es = storage_bytes(opt.storage), plane_bytes = (size_t)nx * (size_t)ny * es;
+            const size_t plane_bytes = (size_t)nx * (size_t)ny * es;
             const bool one_wave = groups <= 64 && (es == 4 ? nx % 16 == 0 && plane_bytes % 1024 != 0 && 5 * groups >= 3 * 64
                                                            : (plane_bytes % 64 != 0 || nx % 32 == 0) && groups >= 52);
             bx4 = std::min(groups, 64);
@@ -691,7 +699,7 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 //                        rows         planes       neither
 //   FP32 walls         6.0 / 6.5    5.5 / 7.3    4.9 / 8.0
 //   FP32 periodic      6.0 / 5.7    5.5 / 6.0    4.9 / 6.3
-//   FP32 on-site       5.6 / 8.4    5.15 / 9.6   4.7, 4.2 / 9.6   (4.2: rows off 16 bytes)
+//   FP32 on-site       5.6 / 8.4    5.6 / 10.2   4.7, 4.2 / 9.6   (4.2: rows off 16 bytes)
 //   16-bit periodic    5.9 / 4.2    5.7 / 4.2    4.5 / 4.4
 //   arrays in the 256 MB cache:
 //   FP32 walls         7.2 / 4.75   7.2 / 4.75   6.5 / 5.25
@@ -706,7 +714,7 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 // 46.2, 96^3 21.1 / 19.4; periodic 256^3 417 / 260, 96^3 20.8 / 15.3; sphere duct
 // 128x128x256 107 / 86 (with a uniform force 91); periodic 256^3 FP16 217 / 180; on-site
 // 256^3 427 / 362, 132x131x131 73.5 / 69.9; but cavity 88^3 16.5 / 18.4, on-site 128^3 57.0 /
-// 57.9, 144^3 83 / 96, 344x258x168 411 / 482 (chosen all the same).
+// 57.9, 144^3 83 / 96, 344x258x168 411 / 482, 260x328x155 357 / 406.
 //
 // 16-bit storage takes pairs only without solid points and beyond the cache: there
 // the kernel is bound by its memory instructions and arithmetic rather than by HBM,
@@ -728,8 +736,8 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     double rate;               // of a single step, bytes per us
     double plane, per1024;     // us of a plane: a part of its own, a part per 1024 work-items
     if (onsite) {
-        rate = align == 0 ? 5.6e6 : align == 1 ? 5.15e6 : nx % 4 == 0 ? 4.7e6 : 4.2e6;
-        plane = align == 0 ? 8.4 : 9.6;
+        rate = align < 2 ? 5.6e6 : nx % 4 == 0 ? 4.7e6 : 4.2e6;
+        plane = align == 0 ? 8.4 : align == 1 ? 10.2 : 9.6;
         per1024 = 0.0;
     } else if (!f32) {
         rate = align == 0 ? 5.9e6 : align == 1 ? 5.7e6 : 4.5e6;
