@@ -328,6 +328,16 @@ bool xcd_eighths(const lbm_lattice* L)
 // us of the whole: 96^3 6015 / 5950 in turn, 112^3 9840 / 9730).
 constexpr size_t XCD_TRAJECTORY_MAX_POINTS = (size_t)1 << 19;
 
+// And for a step that stores rho and u, whose arrays (the last step's are often
+// still in the cache) push the lattice out of it. us per step, eighths / in turn:
+// FP16 118x136x162 (198 MB with 42 MB of rho and u) 54 / 39, FP32 110x134x105 (235 and
+// 25) 60 / 54; but FP16 153x172x93 (186 and 39) 39 / 42, FP32 116x154x77 (209 and 22)
+// 37 / 40.
+bool macros_fit(const lbm_lattice* L)
+{
+    return L->N * ((size_t)2 * Q * storage_bytes(L->storage) + 32) <= (size_t)256 << 20;
+}
+
 // Arguments and launches of the one-step kernels; trajectory: for a rollout or
 // its reverse sweep.
 struct StepLaunches {
@@ -557,10 +567,11 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
     // rows of 105 to 127 points stay on the two-dimensional grid, two to a group.
     // Speed against the one-dimensional grid: cavity 126x225x247 1.17 in bfloat16,
     // 1.10 in FP32, on-site walls 1.14, periodic 1.0; 118x109x364 1.14, 1.06, 1.10, 1.0;
-    // but 141x169x464 0.95, and in place 0.97 to 1.02.
+    // but 141x169x464 0.95, and in place 0.97 to 1.02. (FP32 from where the cache no
+    // longer holds rho and u beside the arrays, 110x134x105 storing them 57 / 54 us.)
     const size_t es = storage_bytes(opt.storage);
     const bool two_rows = opt.pattern == LBM_PATTERN_AB && nx >= 105 && nx < 128 && (size_t)nx * (size_t)ny * es % 64 != 0 &&
-                          2 * (size_t)Q * (size_t)N * es > ((size_t)256 << 20);
+                          (size_t)N * (2 * Q * es + (es == 4 ? 32 : 0)) > ((size_t)256 << 20);
     const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows && !two_rows;
     if (flat1) { bx = 256; by = 1; }
     else if (bx == 0 && by == 0 && rows) { bx = row; by = 1; }
@@ -1608,6 +1619,8 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
     note_capture(L);
     const StepLaunches sl = step_launches(L, from || to);
     const lbmk::StepArgs& args = sl.args;
+    lbmk::StepArgs margs = args;   // of the step that stores rho and u
+    if (rho && !macros_fit(L)) margs.d.xcd = 0u;
     const int fm = collide ? force_mode(L) : lbmk::FORCE_NONE;
     const long long R = (long long)L->events.size();
     if (R > 0 && L->ev_recorded == 0) {
@@ -1652,7 +1665,7 @@ lbm_status run_steps(lbm_lattice* L, int n, bool collide, float* rho, float* u, 
             L->cur ^= 1;
         } else if (L->pattern == LBM_PATTERN_AB) {
             HIPCHK(L, lbmk::launch_step(L->storage, 0, 0, collide, fm, in(s), out(s), L->d_flags,
-                                        L->d_smask, L->d_mmask, L->d_force, args, sl.one, mr, mu, L->onsite));
+                                        L->d_smask, L->d_mmask, L->d_force, mr ? margs : args, sl.one, mr, mu, L->onsite));
             L->cur ^= 1;
         } else {
             HIPCHK(L, lbmk::launch_step(L->storage, 1, L->parity, collide, fm, L->d_f[0], nullptr, L->d_flags,
