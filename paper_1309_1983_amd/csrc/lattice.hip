@@ -598,8 +598,8 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
             // one wave per work-group along x (a whole 256-point row when
             // nx = 256 and vw = 4): the fastest shape measured at 256^3 on MI355X.
             // Rows whose groups do not fill waves (a 260-point row: 65 groups)
-            // take a one-dimensional grid over the plane instead, unless one wave
-            // per row leaves few lanes idle and the other form's waves begin
+            // take a one-dimensional grid over the plane instead, unless a wave of
+            // whole rows leaves few lanes idle and the other form's waves begin
             // anywhere: FP32 rows on 64-byte lines in planes that are no multiple of
             // a wave's 1 KB, and 16-bit planes off the lines or rows on them. MI355X, us per step,
             // one- / two-dimensional: FP32 storing rho and u, 160x253x164 (40 groups) 210 /
@@ -610,10 +610,11 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
             // on the lines, 240x200x149 (60) 0.91 to 0.96 times, 236x200x300 275 / 326.
             const int groups = nx / vw;
             const size_t plane_bytes = (size_t)nx * (size_t)ny * es;
-            const bool one_wave = groups <= 64 && (es == 4 ? nx % 16 == 0 && plane_bytes % 1024 != 0 && 5 * groups >= 3 * 64
-                                                           : (plane_bytes % 64 != 0 || nx % 32 == 0) && groups >= 52);
             bx4 = std::min(groups, 64);
             by4 = std::max(1, 64 / bx4);
+            const int lanes = bx4 * by4;   // of the wave that whole rows fill
+            const bool one_wave = groups <= 64 && (es == 4 ? nx % 16 == 0 && plane_bytes % 1024 != 0 && 5 * lanes >= 3 * 64
+                                                           : (plane_bytes % 64 != 0 || nx % 32 == 0) && lanes >= 52);
             flat = !wave_rows(groups) && !one_wave;
             cpl = vw;
         } else if (bx * by <= 256) {
