@@ -8,9 +8,9 @@
 // first step's arithmetic on units that were idle. Boxes of 16 x 4 x 2 points
 // with one work-item per point of box and halo (432 of 448), so that 32^3
 // gives each of the 256 compute units one work-group. MI355X, us per step, one
-// step per launch / this: 32^3 periodic FP32 3.72 / 2.79, cavity 4.33 / 3.34,
-// 24^3 FP16 3.45 / 2.32, 28^3 duct with a force field 4.43 / 4.23. With more
-// boxes than compute units it loses: 40^3 cavity 5.41 / 5.51, 56^3 8.3 / 9.9.
+// step per launch / this: 32^3 periodic FP32 3.76 / 3.24, cavity 4.39 / 3.60, 24^3
+// FP16 3.89 / 3.18, 28^3 duct with a force field 4.53 / 4.22. With more boxes than
+// compute units it loses: 40^3 cavity 5.01 / 5.57, 56^3 6.3 / 10.0.
 //
 // Per point both steps do the arithmetic of the one-step kernels on values
 // rounded to the storage format in between, so the result is the same bit for

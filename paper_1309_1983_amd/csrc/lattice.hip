@@ -245,10 +245,10 @@ lbmk::Launch launch4_of(const lbm_lattice* L)
 // multiple of 64, or several rows make up a wave. Other rows leave lanes idle
 // there (131 points take three waves, the last with 3 of 64 lanes; 33
 // four-point groups half a wave) and run on a one-dimensional grid over the
-// plane instead. MI355X, us per step, two- against one-dimensional: on-site
-// cavity 132x131x131 (33 groups a row) 99.3 / 82.8; 131x97x75 sphere duct, one
-// point per work-item, FP32 31.1 / 29.6, FP16 20.2 / 18.8; 192^3 duct with a
-// force and rho, u stored (48 groups) 249 / 237.
+// plane instead. MI355X, us per step, two- against one-dimensional: one point per
+// work-item, on-site cavity 132x131x131 94.6 / 72.8, 131x97x75 sphere duct FP16 17.8 /
+// 16.9 (FP32 25.9 / 26.0), 260x259x259 in place 467 / 283; 192^3 duct with a force
+// and rho, u stored (48 four-point groups) 230 / 218.
 bool wave_rows(int n) { return n % 64 == 0 || 64 % n == 0; }
 
 void default_block(int nx, int& bx, int& by)
@@ -308,23 +308,19 @@ lbmk::Launch adjoint_launch(const d3q19::Dims& dims, bool vec_ok, hipStream_t st
 // Whether the one-point kernels give each XCD an eighth of the lattice
 // (point_of): where the arrays fit the memory-side cache, an XCD's L2 then
 // holds much of what its next step reads. MI355X, us per step, groups in turn /
-// eighths: FP32 cavity 48^3 6.96 / 5.66, 96^3 22.7 / 21.3, 112^3 36.2 / 32.2,
-// 120^3 (263 MB) 46.8 / 45.6; FP16 cavity 96^3 16.7 / 15.0, 144^3 41.9 / 38.3;
-// in place FP32 144^3 78.8 / 69.6. Beyond the cache it loses DRAM page locality:
-// 128^3 FP32 53.1 / 57.7, 144^3 82.1 / 83.8. Planes of a multiple of 8 KB lie on
-// the same memory channels in all eighths: 64^3 FP16 6.35 / 6.66, in place 6.61 /
-// 6.92, bfloat16 periodic 5.61 / 6.04, 128^3 FP16 28.3 / 28.3; two FP32 arrays
-// still gain, 64^3 8.89 / 8.63.
+// eighths: FP32 cavity 48^3 6.87 / 5.69, 64^3 8.83 / 8.19, 96^3 22.4 / 20.9, 112^3 35.9 /
+// 31.8, 120^3 (263 MB) 45.6 / 44.1; FP16 cavity 64^3 6.39 / 6.38, 96^3 16.2 / 14.7, 144^3
+// 41.1 / 35.2; in place FP32 144^3 77.7 / 69.3. Beyond the cache it loses DRAM page
+// locality: 128^3 FP32 52.7 / 56.8, 144^3 80.8 / 83.2.
 bool xcd_eighths(const lbm_lattice* L)
 {
-    const bool ab = L->pattern == LBM_PATTERN_AB, f32 = L->storage == LBM_STORAGE_F32;
-    const size_t plane = (size_t)L->dims.nxy * storage_bytes(L->storage);
-    return plane * Q * (size_t)L->nz * (ab ? 2 : 1) <= ((size_t)256 << 20) && (plane % 8192 != 0 || (ab && f32));
+    const size_t arrays = L->pattern == LBM_PATTERN_AB ? 2 : 1;
+    return arrays * Q * L->N * storage_bytes(L->storage) <= ((size_t)256 << 20);
 }
 
 // The same for the launches of a rollout and its reverse sweep, whose states
-// pass through HBM: us per step of both, 48^3 24.7 / 23.3, 77x70x65 47.5 / 45.8,
-// but 96^3 91.5 / 92.7, 112^3 151 / 156 (the recompute steps alone, T = 64, K = 8,
+// pass through HBM: us per step of both, 48^3 24.0 / 22.6, 64^3 34.5 / 34.0, 77x70x65
+// 45.5 / 43.3, but 96^3 90.4 / 91.4, 112^3 149 / 154 (the recompute steps alone, T = 64, K = 8,
 // us of the whole: 96^3 6015 / 5950 in turn, 112^3 9840 / 9730).
 constexpr size_t XCD_TRAJECTORY_MAX_POINTS = (size_t)1 << 19;
 
@@ -972,8 +968,8 @@ lbm_status lbm_create_ex(int nx, int ny, int nz, float tau, const uint8_t* flags
             return fail(LBM_ERR_DEVICE, "compute unit count query: %s", hipGetErrorString(e));
         }
         // small lattices: where every box has a compute unit of its own (us per
-        // step, one step per launch / boxes: 256 boxes of 32^3 3.72 / 2.79; 486
-        // of 36^3 5.02 / 5.01, 350 of 100x20x19 3.75 / 4.68)
+        // step, one step per launch / boxes: 256 boxes of 32^3 3.76 / 3.24, cavity
+        // 4.39 / 3.60; 486 of 36^3 3.91 / 4.32, 350 of 100x20x19 4.34 / 5.37)
         const auto boxes = [](int n, int b) { return (unsigned long long)((n + b - 1) / b); };
         L->box = !L->onsite && boxes(nx, lbmk::BOX_X) * boxes(ny, lbmk::BOX_Y) * boxes(nz, lbmk::BOX_Z) <=
                                    (unsigned long long)cus;
