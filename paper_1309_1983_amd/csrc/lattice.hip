@@ -705,20 +705,24 @@ constexpr int AUTO_GROUPS_PER_CU_ONE_F32 = 5;
 // whole lines on a one-dimensional grid, the tiles' rows do not), or neither. On
 // MI355X, TB/s of a single step / us of a plane of 1024 work-items:
 //                        rows         planes       neither
-//   FP32 walls         6.0 / 6.5    5.5 / 7.3    4.9 / 8.0
-//   FP32 periodic      6.0 / 5.7    5.5 / 6.0    4.9 / 6.3
+//   FP32 walls         5.86 / 6.9   5.6 / 7.35   4.83 / 8.2
+//   FP32 periodic      5.92 / 5.75  5.71 / 5.7   5.01 / 6.55
 //   FP32 on-site       5.6 / 8.4    5.6 / 10.2   4.7, 4.2 / 9.6   (4.2: rows off 16 bytes)
 //   16-bit periodic    5.9 / 4.2    5.7 / 4.2    4.5 / 4.4
 //   arrays in the 256 MB cache:
 //   FP32 walls         7.2 / 4.75   7.2 / 4.75   6.5 / 5.25
 //   FP32 periodic      7.2 / 3.8    7.2 / 3.8    6.5 / 4.3
-// A tile with fewer work-items takes 1.5 us less per 1024 (2.2 periodic from the
-// cache), except beside on-site walls, where the rebuild, which runs in every wave
-// that holds a box side, bounds the plane. A uniform force costs the pair 0.6 us a
-// plane from the cache (its kernel spills); beyond the cache, and for a force
-// field, which a single step reads twice as often, both lose alike. Over 531
-// lattices of 5e5 to 2e7 points the choice is 0.3% slower than the better of the
-// two on average. us per step, single / pair: cavity 256^3 411 / 279, 128^3 53.1 /
+// A tile with fewer work-items takes 1.45 us less per 1024 (2.2 periodic) from the
+// cache, 2.65, 4.2 or 6.2 us beyond it, where lines that two tiles store in part cost
+// more the larger the tile; except beside on-site walls, where the rebuild, which runs
+// in every wave that holds a box side, bounds the plane. Off the lines a plane beyond the
+// cache also takes 0.45 us more for each factor e in the size of the arrays over the cache's, 0.3
+// to 0.4 less with tiles of whole lines, and 1.0 (planes on the lines) or 0.3 more where
+// rows begin off 16 bytes. A uniform force costs the pair 0.6 us a
+// plane from the cache (its kernel spills), 0.1 beyond it; for a force
+// field, which a single step reads twice as often, both lose alike. Over 1190
+// lattices of 5e5 to 2.4e7 points the choice is 0.2% slower than the better of the
+// two on average (0.1% beyond the cache without on-site walls). us per step, single / pair: cavity 256^3 411 / 279, 128^3 53.1 /
 // 46.2, 96^3 21.1 / 19.4; periodic 256^3 417 / 260, 96^3 20.8 / 15.3; sphere duct
 // 128x128x256 107 / 86 (with a uniform force 91); periodic 256^3 FP16 217 / 180; on-site
 // 256^3 427 / 362, 132x131x131 73.5 / 69.9; but cavity 88^3 16.5 / 18.4, on-site 128^3 57.0 /
@@ -741,6 +745,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     const size_t row = (size_t)nx * (f32 ? 4 : 2);
     const bool lines = row % 64 == 0;
     const int align = lines ? 0 : (row * (size_t)ny % 64 == 0 ? 1 : 2);
+    const bool large = f32 && !onsite && !cached;
     double rate;               // of a single step, bytes per us
     double plane, per1024;     // us of a plane: a part of its own, a part per 1024 work-items
     if (onsite) {
@@ -756,9 +761,13 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
         plane = (walls ? 3.3 : 1.6) + (align == 2 ? 0.5 : 0.0) + (uniform_force ? 0.6 : 0.0);
         per1024 = walls ? 1.45 : 2.2;
     } else {
-        rate = align == 0 ? 6.0e6 : align == 1 ? 5.5e6 : 4.9e6;
-        plane = walls ? (align == 0 ? 5.0 : align == 1 ? 5.8 : 6.5) : (align == 0 ? 4.2 : align == 1 ? 4.5 : 4.8);
-        per1024 = 1.5;
+        rate = walls ? (align == 0 ? 5.86e6 : align == 1 ? 5.6e6 : 4.83e6)
+                     : (align == 0 ? 5.92e6 : align == 1 ? 5.71e6 : 5.01e6);
+        plane = (align == 0 ? 3.1 : align == 1 ? 1.5 : 0.35) + (walls ? (align == 0 ? 1.15 : 1.65) : 0.0) +
+                (uniform_force ? 0.1 : 0.0);
+        if (align > 0) plane += 0.45 * std::log(2.0 * N * Q * 4 / (256.0 * (1 << 20))) +
+                                (nx % 4 != 0 ? (align == 1 ? 1.0 : 0.3) : 0.0);
+        per1024 = align == 0 ? 2.65 : align == 1 ? 4.2 : 6.2;
     }
     const double single = N * 2.0 * Q * (f32 ? 4 : 2) / rate + 2.5;
     lbmk::PairShape ps{};
@@ -773,13 +782,17 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
     ps.rows = (uint32_t)((ny + (int)ps.nty - 1) / (int)ps.nty) + 2u;
     ps.nty = (uint32_t)((ny + (int)ps.rows - 3) / ((int)ps.rows - 2));
     ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
-    plane += per1024 * (ps.threads / 1024.0);
+    if (!large) plane += per1024 * (ps.threads / 1024.0);
     // a few columns short of whole 64-byte lines: take them (us per step, before
     // / after: 140x110x150 cavity 47 columns 69.9 / 65.6, 292x192x401 59
     // columns 616 / 574, 245x216x126 periodic 62 columns 148 / 134)
     if (nx % 16 != 0 && ps.tx % 16u >= 11u) {
         ps.tx = (ps.tx + 15u) / 16u * 16u;
         ps.threads = (ps.rows * (ps.tx + 2u) + 63u) / 64u * 64u;
+    }
+    if (large) {
+        plane += per1024 * (ps.threads / 1024.0);
+        if (align > 0 && ps.tx % 16u == 0) plane -= align == 1 ? 0.3 : 0.4;
     }
     double least = 0.0;
     for (int c = 1; c <= nz; ++c) {
@@ -796,7 +809,7 @@ bool plan_pair(int nx, int ny, int nz, int storage, bool walls, bool onsite, boo
             best = ps;
         }
     }
-    return best.groups > 0 && least < (onsite ? 0.95 : 0.98) * 2.0 * single;
+    return best.groups > 0 && least < (onsite ? 0.95 : large ? 1.0 : 0.98) * 2.0 * single;
 }
 
 }  // namespace
