@@ -550,23 +550,26 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
         return fail(LBM_ERR_INVALID, "groups_per_cu must be -1, 0 or 1..64 (got %d)", opt.groups_per_cu);
     int bx = opt.block_x, by = opt.block_y;
     // Rows that do not fill waves: a one-dimensional grid, whose waves store whole
-    // lines where planes begin on them, or one row per work-group where neither
-    // form stores whole lines and the row leaves hardly a lane idle. MI355X, us per
-    // step, a row per work-group / one-dimensional: FP32 cavity 257x256x256 655 / 451,
-    // 380x200x100 263 / 200, 321x300x300 1017 / 898, 511x300x200 1055 / 982 (but
-    // 260x259x259 567 / 585); 16-bit spheres 257x256x256 330 / 238, 444x180x150 229 /
-    // 218, but 383x250x250 441 / 470, 510x150x100 143 / 151, 511x300x200 580 / 606.
+    // lines where planes begin on them. Between two 16-bit arrays that the cache does
+    // not hold, with planes off half lines, rows of more than three waves go one to a
+    // work-group instead: neither form stores whole lines then. Speed of a row per
+    // work-group against the one-dimensional grid, MI355X, mean of 20 to 130 lattices
+    // (arrays over 320 MB): rows of 257 to 512 points, planes off 8 bytes 1.09, off 16
+    // 1.06, off 32 1.02, off 64 0.94, on the lines 0.80; 513 to 850 points 1.11, 1.09,
+    // 1.03; 193 to 255 points 1.03, 1.01, 0.94, 0.93, 0.77; 129 to 191 points 0.97 at
+    // best. Arrays of 256 to 320 MB 1.04 and 1.00, smaller ones 0.90 to 0.99. (FP32
+    // cavity 257x256x256 655 us in rows, 451 one-dimensional; 511x300x200 1055 / 982.)
+    const size_t es = storage_bytes(opt.storage), plane_bytes = (size_t)nx * (size_t)ny * es;
     const int row = (nx + 63) / 64 * 64;
-    const bool rows = opt.pattern == LBM_PATTERN_AB && storage_bytes(opt.storage) == 2 && nx >= 256 && row <= 1024 &&
-                      row - nx <= 4 && (size_t)nx * (size_t)ny % 32 != 0;
+    const bool rows = opt.pattern == LBM_PATTERN_AB && es == 2 && nx > 192 && row <= 1024 &&
+                      plane_bytes % (nx > 256 ? 16 : 8) != 0 && (size_t)N * 2 * Q * es > ((size_t)320 << 20);
     // Between two arrays that the cache does not hold, with planes off the lines,
     // rows of 105 to 127 points stay on the two-dimensional grid, two to a group.
     // Speed against the one-dimensional grid: cavity 126x225x247 1.17 in bfloat16,
     // 1.10 in FP32, on-site walls 1.14, periodic 1.0; 118x109x364 1.14, 1.06, 1.10, 1.0;
     // but 141x169x464 0.95, and in place 0.97 to 1.02. (FP32 from where the cache no
     // longer holds rho and u beside the arrays, 110x134x105 storing them 57 / 54 us.)
-    const size_t es = storage_bytes(opt.storage);
-    const bool two_rows = opt.pattern == LBM_PATTERN_AB && nx >= 105 && nx < 128 && (size_t)nx * (size_t)ny * es % 64 != 0 &&
+    const bool two_rows = opt.pattern == LBM_PATTERN_AB && nx >= 105 && nx < 128 && plane_bytes % 64 != 0 &&
                           (size_t)N * (2 * Q * es + (es == 4 ? 32 : 0)) > ((size_t)256 << 20);
     const bool flat1 = bx == 0 && by == 0 && !wave_rows(nx) && !rows && !two_rows;
     if (flat1) { bx = 256; by = 1; }
@@ -597,20 +600,23 @@ lbm_status resolve_layout(int nx, int ny, int nz, const lbm_options& opt, Layout
             // take a one-dimensional grid over the plane instead, unless a wave of
             // whole rows leaves few lanes idle and the other form's waves begin
             // anywhere: FP32 rows on 64-byte lines in planes that are no multiple of
-            // a wave's 1 KB, and 16-bit planes off the lines or rows on them. MI355X, us per step,
-            // one- / two-dimensional: FP32 storing rho and u, 160x253x164 (40 groups) 210 /
-            // 203, 176x222x174 cavity 1.05 times as fast, 144x218x123 (36 groups) 0.95
-            // times, but 192^3 201 / 207, 160x192x256 225 / 234; 16 bits 228x143x422 (57
-            // groups) cavity 284 / 274, 216x195x191 (54) 131 / 127, 224x139x406 (56) duct with
-            // a force 184 / 175, but 204x293x289 (51) 0.96 to 1.01 times; with planes alone
-            // on the lines, 240x200x149 (60) 0.91 to 0.96 times, 236x200x300 275 / 326.
+            // a wave's 1 KB, and 16-bit planes off the lines or rows on them. MI355X, speed
+            // of the two- against the one-dimensional grid, mean of 40 to 60 FP32 lattices
+            // of 5e6 to 2e7 points with 40, 44, 48, 52, 56 and 60 lanes of a wave in use: cavity
+            // storing rho and u 1.00, 1.02, 1.03, 1.03, 1.02, 1.01, duct with a force field
+            // 0.95, 0.98, 1.00 and more (but 192^3 201 / 207 us per step, 160x192x256 225 /
+            // 234). 16 bits, 44, 52, 56, 60 and more
+            // lanes of a wave in use: planes off half lines 0.99, 1.01, 1.03, 1.04; on them
+            // 0.95, 0.98, 0.98, 1.02; rows on the lines 0.90, 0.96, 1.01; planes alone
+            // on the lines 0.86, 0.92, 0.96, 0.94.
             const int groups = nx / vw;
-            const size_t plane_bytes = (size_t)nx * (size_t)ny * es;
             bx4 = std::min(groups, 64);
             by4 = std::max(1, 64 / bx4);
             const int lanes = bx4 * by4;   // of the wave that whole rows fill
-            const bool one_wave = groups <= 64 && (es == 4 ? nx % 16 == 0 && plane_bytes % 1024 != 0 && 5 * lanes >= 3 * 64
-                                                           : (plane_bytes % 64 != 0 || nx % 32 == 0) && lanes >= 52);
+            bool one_wave = groups <= 64;
+            if (es == 4) one_wave = one_wave && nx % 16 == 0 && plane_bytes % 1024 != 0 && lanes >= 48;
+            else if (nx % 32 == 0) one_wave = one_wave && lanes >= 56;
+            else one_wave = one_wave && plane_bytes % 64 != 0 && lanes >= (plane_bytes % 32 != 0 ? 52 : 60);
             flat = !wave_rows(groups) && !one_wave;
             cpl = vw;
         } else if (bx * by <= 256) {
