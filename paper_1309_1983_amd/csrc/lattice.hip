@@ -663,8 +663,11 @@ bool small_periodic(const lbm_lattice* L) { return !L->walls && L->N <= SMALL_PE
 //  FP32: cavity 64^3 8.9 / 9.5, 96^3 22.7 / 32.1, 144^3 82.7 / 88.1, 176^3 145
 //  / 151, 192^3 189 / 178, 256^3 436 / 409 (412 with the residency cap); periodic 80^3 14.0 / 16.7, 128^3
 //  55 / 60, 192^3 187 / 181; sphere duct 128x128x256 111 / 113, 256^3 444 /
-//  461; on-site walls 132x131x131 73 / 83, 128^3 57 / 70, 148x200x200 162 / 172, but
-//  192^3 204 / 196, 236^3 370 / 352, 348x300x89 261 / 251 (256^3 426 / 437).
+//  461; on-site walls 132x131x131 73 / 83, 128^3 57 / 70, 148x200x200 162 / 172, 256^3
+//  427 / 437, 240x159x226 230 / 240, and over 240 lattices of 5e6 to 2e7 points 0.85 to 1.0
+//  times as long with rows on the 64-byte lines (but 192^3 204 / 195), 0.93 to 1.03 with
+//  planes on them up to 8e6 points, 1.02 and more beyond (236^3 372 / 355), 1.00 to 1.05
+//  with neither.
 //  16 bits: cavity 64^3 6.4 / 10.7, 128^3 28 / 33, 192^3 96 / 104, 256^3 219 /
 //  225, 384x200x200 208 / 208, 512^3 1862 / 1758, 168^3 69 / 72 but 224^3 188 /
 //  160 (rows of 3.5 waves); sphere duct 128x128x256 59 / 63 (bfloat16 with a
@@ -691,6 +694,7 @@ bool one_point(const lbm_lattice* L, double near_fraction)
     if (L->box) return walls && (f32 || L->nx < 256);
     if (!f32) return !L->walls || N <= (walls ? 3u << 20 : 6000000u) || (L->nx % 64 == 0 && L->nx < 512);
     if (!L->walls && !lines && N <= 300000) return false;
+    if (L->onsite) return lines || N <= (L->dims.nxy % 16 == 0 ? 8000000 : 5000000);
     return (porous && lines) || N <= (walls || lines ? 5000000 : 2500000);
 }
 // Resident work-groups per compute unit of the FP32 multi-point AB step (one
